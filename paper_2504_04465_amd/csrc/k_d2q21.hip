@@ -26,10 +26,12 @@ __global__ void __launch_bounds__(BLOCK) k_collide_mlp(const KArgs a) {
   constexpr int Q = L::Q;
   __shared__ MlpInfer W;
   __shared__ uint32_t nbs[BLOCK / 64][Brick<L>::NBP];
+  __shared__ double etab[EXP_TAB];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int64_t t = xcd_block() * BLOCK + threadIdx.x;
   const bool live = t < a.count;  // whole wavefronts
   const int64_t c = a.begin + (live ? t : 0);
+  stage_exp_tab(etab);
   const int32_t brick = stage_bricks<L, S>(a.topo, nbs, c, live);
   const uint8_t fl = live ? a.flags[c] : (uint8_t)F_HOLE;
   const bool valid = !(fl & F_HOLE);
@@ -81,7 +83,8 @@ __global__ void __launch_bounds__(BLOCK) k_collide_mlp(const KArgs a) {
 #pragma unroll
           for (int k = 0; k < NLAM; ++k) lam[k] = 0.0;
         it = newton_lean<L, C>((double)u[0], (double)u[1], (double)T, lam, a.ph.newton_tol, a.ph.newton_max_it,
-                               attempt == 0 ? 1 : 0, attempt == 0 ? a.ph.fallback_tol : a.ph.newton_tol, e);
+                               attempt == 0 ? 1 : 0, attempt == 0 ? a.ph.fallback_tol : a.ph.newton_tol, e,
+                               etab);
         if (attempt == 0 && it != 1) count_add(a.counters, CNT_MLP_FALLBACK, 1);
         if (it >= 0) break;
       }
@@ -90,8 +93,8 @@ __global__ void __launch_bounds__(BLOCK) k_collide_mlp(const KArgs a) {
       count_hist(a.counters, it);
     } else {
       // the network's multipliers as they are
-      double G[NLAM];
-      expo_pass<L, C, false>(lam, (double)u[0], (double)u[1], (double)T, G, nullptr, e);
+      MomSums m;
+      expo_sums<L, C>(lam, etab, m, e);
     }
     C feq[Q], geq[Q];
     const C kg = ((C)2 * (C)a.ph.Cv - (C)L::D) * T;

@@ -24,6 +24,7 @@
 #include "grid_builder.h"
 #include "lattice.h"
 #include "ops.h"
+#include "newton.cuh"
 
 namespace lbm {
 
@@ -758,262 +759,6 @@ __device__ inline void rr_hermite3(C *f, C rho, C rhop, const C *u, const C (&P)
 }
 
 // ---------------------------------------------------------------------------
-// numerical (entropy-maximising) equilibrium, D2Q21: f_eq = rho exp(-(1 +
-// lambda . m_i)) under the eight moment constraints; Newton with a Cholesky
-// step and backtracking on ||G||_2, FP64
-// ---------------------------------------------------------------------------
-template <class L>
-__device__ constexpr double mvec(int i, int a) {
-  const double x = L::S.v[i].x, y = L::S.v[i].y, n2 = x * x + y * y;
-  return a == 0 ? 1.0 : a == 1 ? x : a == 2 ? y : a == 3 ? x * x : a == 4 ? x * y : a == 5 ? y * y
-       : a == 6 ? x * n2 : y * n2;
-}
-
-// One pass over the populations at multipliers lam (Eq. exponential):
-// e_i = exp(-(1 + lam . m_i)), the constraint residuals
-// G_a = sum_i e_i m_ia - M_a (Eqs. G0_8mom - G3yaa_8mom, per unit density)
-// and the Newton matrix H = sum_i e_i m_i m_i^T (packed lower triangle).
-// e_i is kept only in the collision precision C, for the final equilibrium,
-// so that no FP64 population array stays live across the solve.
-template <class L>
-__device__ inline void targets(double ux, double uy, double T, double *M);
-
-// Reflection orbits of a 2-D lattice symmetric under x -> -x and y -> -y:
-// representative k is the k-th velocity with c_x >= 0 and c_y >= 0.
-template <class L>
-__device__ constexpr int n_reps() {
-  int n = 0;
-  for (int i = 0; i < L::Q; ++i) n += (L::S.v[i].x >= 0 && L::S.v[i].y >= 0);
-  return n;
-}
-template <class L>
-__device__ constexpr int rep_of(int i) {
-  const int a = iabs_c(L::S.v[i].x), b = iabs_c(L::S.v[i].y);
-  int k = 0;
-  for (int j = 0; j < L::Q; ++j)
-    if (L::S.v[j].x >= 0 && L::S.v[j].y >= 0) {
-      if (L::S.v[j].x == a && L::S.v[j].y == b) return k;
-      ++k;
-    }
-  return -1;
-}
-template <class L>
-__device__ constexpr int rep_comp(int k, int d) {
-  int n = 0;
-  for (int j = 0; j < L::Q; ++j)
-    if (L::S.v[j].x >= 0 && L::S.v[j].y >= 0) {
-      if (n == k) return d == 0 ? L::S.v[j].x : L::S.v[j].y;
-      ++n;
-    }
-  return 0;
-}
-__device__ constexpr double ipow_c(int a, int p) {
-  double r = 1.0;
-  for (int k = 0; k < p; ++k) r *= a;
-  return r;
-}
-// m_a = sum of terms c x^p y^q: (1, x, y, x^2, xy, y^2, x^3 + x y^2, x^2 y + y^3)
-__device__ constexpr int mterms(int a) { return a >= 6 ? 2 : 1; }
-__device__ constexpr int mterm_p(int a, int t) {
-  return a == 0 ? 0 : a == 1 ? 1 : a == 2 ? 0 : a == 3 ? 2 : a == 4 ? 1 : a == 5 ? 0 : a == 6 ? (t ? 1 : 3)
-       : (t ? 0 : 2);
-}
-__device__ constexpr int mterm_q(int a, int t) {
-  return a == 0 ? 0 : a == 1 ? 0 : a == 2 ? 1 : a == 3 ? 0 : a == 4 ? 1 : a == 5 ? 2 : a == 6 ? (t ? 2 : 0)
-       : (t ? 3 : 1);
-}
-
-// One pass over the populations at multipliers lam (Eq. exponential):
-// e_i = exp(-(1 + lam . m_i)), the constraint residuals
-// G_a = sum_i e_i m_ia - M_a (Eqs. G0_8mom - G3yaa_8mom, per unit density)
-// and the Newton matrix H = sum_i e_i m_i m_i^T (packed lower triangle).
-// The sums go through the reflection orbits: per representative velocity
-// (a, b), the four sign-weighted sums P = sum e, sum s_x e, sum s_y e,
-// sum s_x s_y e over its members give every moment
-// S_pq = sum_i e_i c_x^p c_y^q = sum_k a^p b^q P_k[p mod 2, q mod 2],
-// and G, H are short sums of S.  e_i is kept only in the collision precision
-// C, for the final equilibrium.
-template <class L, class C, bool HESS = true>
-__device__ inline void expo_pass(const double *lam, double ux, double uy, double T, double *G, double *H, C *e) {
-  constexpr int NR = n_reps<L>();
-  double P[NR][4];
-#pragma unroll
-  for (int k = 0; k < NR; ++k)
-#pragma unroll
-    for (int t = 0; t < 4; ++t) P[k][t] = 0.0;
-#pragma unroll
-  for (int i = 0; i < L::Q; ++i) {
-    double s = 1.0;
-#pragma unroll
-    for (int a = 0; a < NLAM; ++a)
-      if (mvec<L>(i, a) != 0.0) s += lam[a] * mvec<L>(i, a);
-    const double ei = exp(-s);
-    e[i] = (C)ei;
-    const int k = rep_of<L>(i);
-    const bool nx = L::S.v[i].x < 0, ny = L::S.v[i].y < 0;
-    P[k][0] += ei;
-    if (rep_comp<L>(k, 0) != 0) P[k][1] += nx ? -ei : ei;
-    if (rep_comp<L>(k, 1) != 0) P[k][2] += ny ? -ei : ei;
-    if (rep_comp<L>(k, 0) != 0 && rep_comp<L>(k, 1) != 0) P[k][3] += (nx != ny) ? -ei : ei;
-  }
-  // S_pq for p + q <= 6
-  double S[7][7];
-#pragma unroll
-  for (int p = 0; p <= 6; ++p)
-#pragma unroll
-    for (int q = 0; p + q <= 6; ++q) {
-      double acc = 0.0;
-#pragma unroll
-      for (int k = 0; k < NR; ++k) {
-        const double cf = ipow_c(rep_comp<L>(k, 0), p) * ipow_c(rep_comp<L>(k, 1), q);
-        if (cf != 0.0) acc += cf * P[k][(p & 1) | ((q & 1) << 1)];
-      }
-      S[p][q] = acc;
-    }
-  double M[NLAM];
-  targets<L>(ux, uy, T, M);
-#pragma unroll
-  for (int a = 0; a < NLAM; ++a) {
-    double g = 0.0;
-#pragma unroll
-    for (int t = 0; t < mterms(a); ++t) g += S[mterm_p(a, t)][mterm_q(a, t)];
-    G[a] = g - M[a];
-  }
-  if (HESS)
-#pragma unroll
-    for (int a = 0; a < NLAM; ++a)
-#pragma unroll
-      for (int b = 0; b <= a; ++b) {
-        double h = 0.0;
-#pragma unroll
-        for (int t = 0; t < mterms(a); ++t)
-#pragma unroll
-          for (int u = 0; u < mterms(b); ++u)
-            h += S[mterm_p(a, t) + mterm_p(b, u)][mterm_q(a, t) + mterm_q(b, u)];
-        H[a * (a + 1) / 2 + b] = h;
-      }
-}
-
-__device__ inline double nrm2_8(const double *G) {
-  double s = 0.0;
-#pragma unroll
-  for (int a = 0; a < NLAM; ++a) s += G[a] * G[a];
-  return s;
-}
-
-// largest |G_a|; a NaN propagates so that it never passes a tolerance test
-__device__ inline double nrmmax_8(const double *G) {
-  double s = 0.0;
-#pragma unroll
-  for (int a = 0; a < NLAM; ++a) {
-    const double v = fabs(G[a]);
-    s = (v > s || v != v) ? v : s;
-  }
-  return s;
-}
-
-template <class L>
-__device__ inline void targets(double ux, double uy, double T, double *M) {
-  const double uu = ux * ux + uy * uy;
-  M[0] = 1.0;
-  M[1] = ux;
-  M[2] = uy;
-  M[3] = ux * ux + T;
-  M[4] = ux * uy;
-  M[5] = uy * uy + T;
-  M[6] = ux * (uu + 4.0 * T);
-  M[7] = uy * (uu + 4.0 * T);
-}
-
-// d = H^-1 G by an in-place Cholesky factorisation of the packed H (the
-// diagonal holds the reciprocals 1 / L_jj, so the solves multiply); false
-// when H is not numerically positive definite
-__device__ inline bool cholesky_solve(double *H, const double *G, double *d) {
-#pragma unroll
-  for (int j = 0; j < NLAM; ++j) {
-    double t = H[j * (j + 1) / 2 + j];
-#pragma unroll
-    for (int k = 0; k < j; ++k) t -= H[j * (j + 1) / 2 + k] * H[j * (j + 1) / 2 + k];
-    if (!(t > 0.0)) return false;
-    const double inv = rsqrt(t);
-    H[j * (j + 1) / 2 + j] = inv;
-#pragma unroll
-    for (int i = j + 1; i < NLAM; ++i) {
-      double s = H[i * (i + 1) / 2 + j];
-#pragma unroll
-      for (int k = 0; k < j; ++k) s -= H[i * (i + 1) / 2 + k] * H[j * (j + 1) / 2 + k];
-      H[i * (i + 1) / 2 + j] = s * inv;
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < NLAM; ++i) {
-    double s = G[i];
-#pragma unroll
-    for (int k = 0; k < i; ++k) s -= H[i * (i + 1) / 2 + k] * d[k];
-    d[i] = s * H[i * (i + 1) / 2 + i];
-  }
-#pragma unroll
-  for (int i = NLAM - 1; i >= 0; --i) {
-    double s = d[i];
-#pragma unroll
-    for (int k = i + 1; k < NLAM; ++k) s -= H[k * (k + 1) / 2 + i] * d[k];
-    d[i] = s * H[i * (i + 1) / 2 + i];
-  }
-  return true;
-}
-
-// Newton-Raphson on the eight constraints from the multipliers in lam, with
-// backtracking on the 2-norm of the residual (at most 30 halvings).  The
-// stopping test max_a |G_a| <= tol is applied before every step; the first
-// min_steps steps are always taken, and after exactly min_steps steps the
-// looser tolerance tol_first applies (the surrogate's single correction).
-// Returns the number of steps, or -1 (not converged within max_it, or H not
-// positive definite).  e receives exp(-(1 + lam . m_i)) at the final lam.
-template <class L, class C>
-__device__ inline int newton_lean(double ux, double uy, double T, double *lam, double tol, int max_it,
-                                  int min_steps, double tol_first, C *e) {
-  double G[NLAM], H[NLAM * (NLAM + 1) / 2], d[NLAM], base[NLAM];
-  // one evaluation site: each pass either checks a new iterate or tests a
-  // trial point of the line search
-  int it = 0, h = 0;
-  bool trial = false;
-  double n0 = 0.0, alpha = 1.0;
-  for (;;) {
-    expo_pass<L, C>(lam, ux, uy, T, G, H, e);
-    if (trial) {
-      if (!(nrm2_8(G) < n0) && h < 30) {
-        ++h;
-        alpha *= 0.5;
-#pragma unroll
-        for (int a = 0; a < NLAM; ++a) lam[a] = base[a] + alpha * d[a];
-        continue;
-      }
-      trial = false;
-      ++it;
-    }
-    if (it >= min_steps && nrmmax_8(G) <= (it == min_steps && min_steps > 0 ? tol_first : tol)) return it;
-    if (it == max_it) return -1;
-    if (!cholesky_solve(H, G, d)) return -1;
-    n0 = nrm2_8(G);
-    alpha = 1.0;
-    h = 0;
-#pragma unroll
-    for (int a = 0; a < NLAM; ++a) {
-      base[a] = lam[a];
-      lam[a] = base[a] + alpha * d[a];
-    }
-    trial = true;
-  }
-}
-
-// cold-or-warm Newton solve to tol (the paper's solver); FP64 equilibrium out
-template <class L>
-__device__ inline int newton_solve(double ux, double uy, double T, double *lam, double tol, int max_it,
-                                   double *e) {
-  return newton_lean<L, double>(ux, uy, T, lam, tol, max_it, 0, tol, e);
-}
-
-// ---------------------------------------------------------------------------
 // kinetic sensor, Eqs. DeltaAvg and shock_function
 // ---------------------------------------------------------------------------
 template <class L, class C>
@@ -1148,9 +893,10 @@ __device__ inline void cell_moments_shifted(const C *h, C &rho1, C &rho, C (&u)[
 }
 
 // equilibrium of any model at a macroscopic state; Newton family updates lam
+// (tab: the exponential's table, in LDS where the kernel has staged it)
 template <class L, int COLL, class C>
 __device__ inline int equilibrium_any(C rho, const C *u, C T, const PhysArgs &ph, double *lam,
-                                      bool warm, C *feq, C *geq) {
+                                      bool warm, C *feq, C *geq, const double *tab = exp_tab_g) {
   int it = 0;
   if constexpr (COLL == COLL_BGK || COLL == COLL_RR) {
     if constexpr (product_basis<L>()) equilibrium_product<L, C>(rho, u, feq);
@@ -1163,7 +909,7 @@ __device__ inline int equilibrium_any(C rho, const C *u, C T, const PhysArgs &ph
       for (int a = 0; a < NLAM; ++a) lam[a] = 0.0;
     C e[L::Q];
     it = newton_lean<L, C>((double)u[0], (double)u[1], (double)T, lam, ph.newton_tol, ph.newton_max_it, 0,
-                           ph.newton_tol, e);
+                           ph.newton_tol, e, tab);
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) feq[i] = rho * e[i];
   }
@@ -1240,6 +986,7 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
   constexpr int Q = L::Q;
   constexpr int CB = CollideBlock<L, COLL>::value;
   __shared__ uint32_t nbs[CB / 64][Brick<L>::NBP];
+  __shared__ double etab[COLL >= COLL_DDF_NEWTON ? EXP_TAB : 1];
   int64_t blk, begin = a.begin, count = a.count;
   const void *fin_p = a.fin, *gin_p = a.gin;
   void *fout_p = a.fout, *gout_p = a.gout;
@@ -1277,6 +1024,7 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
   // (a vector load of the wavefront's one mask: a scalar load would be
   // sunk past the barrier to its first use)
   const uint64_t xm = a.topo.xmask[c >> 6];
+  if constexpr (COLL >= COLL_DDF_NEWTON) stage_exp_tab(etab);
   const int32_t brick = stage_bricks<L, S>(a.topo, nbs, c, live);
   if (!live) return;
   if (fl & F_HOLE) return;
@@ -1371,7 +1119,7 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
           park[wv][Q + i][ln] = g[i];
         }
         asm volatile("" ::: "memory");
-        it = equilibrium_any<L, COLL, C>(rhop, u, T, a.ph, lam, a.ph.warm != 0, feq, geq);
+        it = equilibrium_any<L, COLL, C>(rhop, u, T, a.ph, lam, a.ph.warm != 0, feq, geq, etab);
         asm volatile("" ::: "memory");
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
