@@ -74,7 +74,6 @@ __global__ void __launch_bounds__(BLOCK) k_collide_mlp(const KArgs a) {
       // residual then exceeds fallback_tol, Newton continues from the
       // corrected multipliers to newton_tol (from zero if the correction
       // itself failed)
-      count_add(a.counters, CNT_NEWTON_CALLS, 1);
       // one call site for both attempts (a second inlined solver would
       // raise the kernel's register need)
       int it = -1;
@@ -88,9 +87,7 @@ __global__ void __launch_bounds__(BLOCK) k_collide_mlp(const KArgs a) {
         if (attempt == 0 && it != 1) count_add(a.counters, CNT_MLP_FALLBACK, 1);
         if (it >= 0) break;
       }
-      if (it < 0) count_add(a.counters, CNT_NEWTON_FAIL, 1);
-      else count_add(a.counters, CNT_NEWTON_ITERS, (unsigned long long)it);
-      count_hist(a.counters, it);
+      count_solves(a.counters, it);
     } else {
       // the network's multipliers as they are
       MomSums m;

@@ -761,12 +761,22 @@ __device__ inline void rr_hermite3(C *f, C rho, C rhop, const C *u, const C (&P)
 // ---------------------------------------------------------------------------
 // kinetic sensor, Eqs. DeltaAvg and shock_function
 // ---------------------------------------------------------------------------
+// n / d for the sensor's mean of Q ratios: the hardware reciprocal and one
+// correction of the quotient (within an ulp; d is at least 1e-30), 4
+// instructions where the IEEE division takes 10
+__device__ inline float ratio(float n, float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  const float q = n * r;
+  return __builtin_fmaf(__builtin_fmaf(-q, d, n), r, q);
+}
+__device__ inline double ratio(double n, double d) { return n / d; }
+
 template <class L, class C>
 __device__ inline C sensor_alpha(const C *f, const C *feq, C tau, C A) {
   constexpr C tiny = sizeof(C) == 8 ? (C)1e-300 : (C)1e-30;
   C eps = (C)0;
 #pragma unroll
-  for (int i = 0; i < L::Q; ++i) eps += fabs(f[i] - feq[i]) / fmax(fabs(feq[i]), tiny);
+  for (int i = 0; i < L::Q; ++i) eps += ratio(fabs(f[i] - feq[i]), fmax(fabs(feq[i]), tiny));
   eps *= (C)(1.0 / L::Q);
   return eps < (C)0.01 ? (C)1 : eps < (C)0.1 ? (C)1.05 : eps < (C)1 ? A : (C)1 / tau;
 }
@@ -925,20 +935,33 @@ __device__ inline void count_add(unsigned long long *ctr, int which, unsigned lo
   if (v) atomicAdd(ctr + CNT_COUNT * (blockIdx.x & (CNT_COPIES - 1u)) + which, v);
 }
 
-// Histogram of the Newton steps per solve (the per-cell iteration counts
-// the paper keeps to monitor stability, Sec. 4.4): bin k < NHIST - 1 counts
-// solves of k steps, the last bin longer solves and failures (it < 0).  The
-// active lanes of a wavefront add one atomic per distinct bin.
-__device__ inline void count_hist(unsigned long long *ctr, int it) {
-  const int bin = (it < 0 || it >= NHIST - 1) ? NHIST - 1 : it;
-  unsigned long long *base = ctr + CNT_COUNT * (blockIdx.x & (CNT_COPIES - 1u)) + CNT_HIST0;
+// A solve of `it` steps (it < 0: it failed) of every active lane: calls,
+// steps, failures and the histogram of the steps per solve (the per-cell
+// iteration counts the paper keeps to monitor stability, Sec. 4.4: bin
+// k < NHIST - 1 counts solves of k steps, the last bin longer solves and
+// failures).  The wavefront goes through the distinct step counts of its
+// lanes, two or three of them, with scalar arithmetic, and adds one atomic
+// per count and total.
+__device__ inline void count_solves(unsigned long long *ctr, int it) {
   uint64_t todo = __ballot(1);
+  const bool lead = (int)(threadIdx.x & 63) == __ffsll((unsigned long long)todo) - 1;
+  unsigned long long *base = ctr + CNT_COUNT * (blockIdx.x & (CNT_COPIES - 1u));
+  unsigned long long calls = 0, steps = 0, failed = 0;
   while (todo) {
-    const int lead = __ffsll((unsigned long long)todo) - 1;
-    const int b = __shfl(bin, lead);
-    const uint64_t same = __ballot(bin == b) & todo;
-    if ((int)(threadIdx.x & 63) == lead) atomicAdd(base + b, (unsigned long long)__popcll(same));
+    const int v = __builtin_amdgcn_readlane(it, __ffsll((unsigned long long)todo) - 1);
+    const uint64_t same = __ballot(it == v) & todo;
+    const unsigned long long n = (unsigned long long)__popcll(same);
+    const int bin = (v < 0 || v >= NHIST - 1) ? NHIST - 1 : v;
+    if (lead) atomicAdd(base + CNT_HIST0 + bin, n);
+    calls += n;
+    if (v < 0) failed += n;
+    else steps += (unsigned long long)v * n;
     todo &= ~same;
+  }
+  if (lead) {
+    atomicAdd(base + CNT_NEWTON_CALLS, calls);
+    if (steps) atomicAdd(base + CNT_NEWTON_ITERS, steps);
+    if (failed) atomicAdd(base + CNT_NEWTON_FAIL, failed);
   }
 }
 
@@ -1130,10 +1153,7 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
         it = equilibrium_any<L, COLL, C>(rhop, u, T, a.ph, lam, a.ph.warm != 0, feq, geq);
       }
       if constexpr (COLL >= COLL_DDF_NEWTON) {
-        count_add(a.counters, CNT_NEWTON_CALLS, 1);
-        if (it < 0) count_add(a.counters, CNT_NEWTON_FAIL, 1);
-        else count_add(a.counters, CNT_NEWTON_ITERS, (unsigned long long)it);
-        count_hist(a.counters, it);
+        count_solves(a.counters, it);
 #pragma unroll
         for (int k = 0; k < NLAM; ++k) ((LamT<S> *)a.lam)[(int64_t)k * a.stride + c] = (LamT<S>)lam[k];
       }

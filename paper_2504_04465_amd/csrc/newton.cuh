@@ -210,7 +210,9 @@ __device__ inline void orbits(std::integer_sequence<int, K...>, const double *la
 // for the final equilibrium.
 template <class L, class C>
 __device__ inline void expo_sums(const double *lam, const double *tab, MomSums &m, C *e) {
-  m = MomSums{};
+  // -0.0 is the neutral element of addition, so the first terms cost nothing
+  m = MomSums{-0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0,
+              -0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0, -0.0};
   orbits<L, C>(std::make_integer_sequence<int, orbit_count<L>()>{}, lam, 1.0 + lam[0], tab, m, e);
 }
 
@@ -262,6 +264,15 @@ __device__ inline double nrmmax_8(const double *G) {
   return s;
 }
 
+// 1 / sqrt(t) of a normal positive t to about an ulp: the hardware's estimate
+// and one third-order correction (no special cases: the factorisation tests
+// its pivots itself)
+__device__ inline double rsqrt_pivot(double t) {
+  const double y = __builtin_amdgcn_rsq(t);
+  const double e = __builtin_fma(-t * y, y, 1.0);
+  return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
+
 // d = H^-1 G by an in-place Cholesky factorisation of the packed H (the
 // diagonal holds the reciprocals 1 / L_jj, so the solves multiply); false
 // when H is not numerically positive definite (d is then of no use; a test
@@ -275,7 +286,7 @@ __device__ inline bool cholesky_solve(double *H, const double *G, double *d) {
 #pragma unroll
     for (int k = 0; k < j; ++k) t -= H[j * (j + 1) / 2 + k] * H[j * (j + 1) / 2 + k];
     ok = ok && t > 0.0;
-    const double inv = rsqrt(t);
+    const double inv = rsqrt_pivot(t);
     H[j * (j + 1) / 2 + j] = inv;
 #pragma unroll
     for (int i = j + 1; i < NLAM; ++i) {
@@ -315,8 +326,8 @@ template <class L, class C>
 __device__ inline int newton_lean(double ux, double uy, double T, double *lam, double tol, int max_it,
                                   int min_steps, double tol_first, C *e, const double *tab) {
   double d[NLAM];
-  // one evaluation site: each pass either checks a new iterate or tests a
-  // trial point of the line search
+  // one evaluation site and one way round: each pass either tests a trial
+  // point of the line search or takes a step from an accepted iterate
   int it = 0, h = 0;
   bool trial = false;
   double n0 = 0.0, alpha = 1.0;
@@ -326,28 +337,25 @@ __device__ inline int newton_lean(double ux, double uy, double T, double *lam, d
     double G[NLAM];
     residual8(m, ux, uy, T, G);
     const double n1 = nrm2_8(G);
-    if (trial) {
-      if (!(n1 < n0) && h < 30) {
-        ++h;
-        alpha *= 0.5;
-#pragma unroll
-        for (int a = 0; a < NLAM; ++a) lam[a] -= alpha * d[a];
-        continue;
-      }
-      trial = false;
-      ++it;
+    double step;
+    if (trial && !(n1 < n0) && h < 30) {
+      ++h;
+      alpha *= 0.5;
+      step = -alpha;
+    } else {
+      if (trial) ++it;
+      if (it >= min_steps && nrmmax_8(G) <= (it == min_steps && min_steps > 0 ? tol_first : tol)) return it;
+      if (it == max_it) return -1;
+      double H[NLAM * (NLAM + 1) / 2];
+      newton_matrix(m, H);
+      if (!cholesky_solve(H, G, d)) return -1;
+      n0 = n1;
+      step = alpha = 1.0;
+      h = 0;
+      trial = true;
     }
-    if (it >= min_steps && nrmmax_8(G) <= (it == min_steps && min_steps > 0 ? tol_first : tol)) return it;
-    if (it == max_it) return -1;
-    double H[NLAM * (NLAM + 1) / 2];
-    newton_matrix(m, H);
-    if (!cholesky_solve(H, G, d)) return -1;
-    n0 = n1;
-    alpha = 1.0;
-    h = 0;
 #pragma unroll
-    for (int a = 0; a < NLAM; ++a) lam[a] += d[a];
-    trial = true;
+    for (int a = 0; a < NLAM; ++a) lam[a] = __builtin_fma(step, d[a], lam[a]);
   }
 }
 
