@@ -1213,34 +1213,41 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
 }
 
 // ---------------------------------------------------------------------------
-// coalescence (Eq. coalescence): 2^D lanes per coarse ghost, one per child;
-// each lane pulls the child's population as the fine level's next update
-// would, the lanes of a ghost are summed with wavefront shuffles
+// Interface and boundary kernels: a lane takes POPS populations of one ghost
+// child (or boundary cell), the populations uniform over the block (block
+// row y: populations y POPS, ...).  A launch touches a thin layer of cells
+// and is a chain of dependent reads (child -> pull source -> value -> store),
+// so its time is that chain, not its bytes.  With a lane per child, which
+// walked or unrolled all populations, the coalescence of an airfoil
+// interface (D2Q21, 6 k ghosts) took 20.8 us, of the 4096 x 8 shock tube
+// 8.2 us; with one population per lane 7.6 and 4.0 us.
+// POPS = 1 below POPS_WIDE lanes, where the lanes of one population leave
+// compute units idle.  Above, a lane's table reads serve several populations,
+// whose loads are in flight together: four for the coalescence (sphere, 31 k
+// ghosts of 8 children: 29.3 us a launch with one, 26.2 with four, 28.2 with
+// all 27) and the boundary fill, all of them for the explosion's plain copy
+// (18.2 us with one, 12.8 with four, 11.5 with all).  On the cylinder's
+// interfaces (up to 37 k lanes) four instead of one cost 2.5 % of the step.
 // ---------------------------------------------------------------------------
+constexpr int64_t POPS_WIDE = 65536;
+
+// coalescence (Eq. coalescence): each lane pulls its child's population as
+// the fine level's next update would; the 2^D lanes of a ghost are summed
+// with wavefront shuffles.
 // In place (AAF = 2: the fine level at an odd phase, its rows swapped) the
 // children are read as that level's swapped pull; SW: the coarse level is at
 // an odd phase and reads population i of its coalesced slot from row opp(i).
-template <class L, class S, bool PRE, bool DDF, bool LAM, int AAF = 0, bool SW = false>
+template <int POPS, class L, class S, bool PRE, bool DDF, bool LAM, int AAF = 0, bool SW = false>
 __global__ void __launch_bounds__(BLOCK) k_coalesce(const CArgs a) {
   using C = typename Sto<S>::C;
   constexpr int NCH = 1 << L::D;
   const int64_t t = (int64_t)blockIdx.x * BLOCK + threadIdx.x;
-  // lanes (ghost, group, child): group k of ngrp takes the populations
-  // i = k mod ngrp, so that a small interface still spreads over many
-  // compute units
-  const int64_t q = t / NCH;
-  const int64_t gl = q / a.ngrp;
-  const int grp = (int)(q % a.ngrp);
+  const int64_t gl = t / NCH;
   const bool valid = gl < a.count;
   const int64_t gk = a.g0 + gl;
   const int32_t ch = valid ? a.child[gk * NCH + (t % NCH)] : -1;
   const int32_t crow = ch >= 0 ? a.crow[gk * NCH + (t % NCH)] : 0;
-  uint64_t mask = valid ? a.unknown[gk] : 0ull;
-  if (a.ngrp > 1) {
-    uint64_t sel = 0ull;
-    for (int i = grp; i < L::Q; i += a.ngrp) sel |= 1ull << i;
-    mask &= sel;
-  }
+  const uint64_t mask = valid ? a.unknown[gk] : 0ull;
   const bool lead = valid && (t % NCH) == 0;
   const C nf = group_sum<NCH, C>(ch >= 0 ? (C)1 : (C)0);
   const S *fin = (const S *)a.fin_child;
@@ -1248,64 +1255,50 @@ __global__ void __launch_bounds__(BLOCK) k_coalesce(const CArgs a) {
   S *fout = (S *)a.fout_coarse;
   S *gout = (S *)a.gout_coarse;
   const int64_t slot = a.vbase + gk;
-  if (a.ngrp > 1) {
-    // a small interface: the lane's own populations one at a time.  The
-    // unrolled path below is tens of KB of code for the wide lattices, and
-    // its cold instruction fetch dominates a launch of a few workgroups.
-    // The NCH lanes of a group share grp and so the trip count.
-    for (int i = grp == 0 ? a.ngrp : grp; i < L::Q; i += a.ngrp) {
-      const bool need = (mask >> i) & 1ull;
-      C v = (C)0, vg = (C)0;
-      if (need && ch >= 0) {
-        const int32_t sv = a.xnbr[(int64_t)(i - 1) * a.xstride + crow];
-        int64_t idx;
-        const int64_t ri = AAF == 2 ? L::S.opp[i] : i, ro = AAF == 2 ? i : L::S.opp[i];
-        if (PRE) idx = pix<L::Q>(i, (int64_t)sv >= a.vbase ? (int64_t)sv : (int64_t)ch);
-        else idx = sv >= 0 ? pix<L::Q>(ri, sv) : pix<L::Q>(ro, ch);
-        v = Sto<S>::ld(fin, idx, L::S.w[i]);
-        if (DDF) vg = Sto<S>::ld(gin, idx, 0.0);
-        if (!PRE && sv <= -2)
-          v += (C)(2.0 * L::S.w[i] * (wall_dot<L>(a.uw, -2 - sv, i) + noise_dot(a.xdu, a.xstride, crow, i)) /
-                   a.cs2w);
-      }
-      v = group_sum<NCH, C>(v);
-      if (DDF) vg = group_sum<NCH, C>(vg);
-      if (lead && need) {
-        const int64_t r = SW ? L::S.opp[i] : i;
-        Sto<S>::st(fout, pix<L::Q>(r, slot), v / nf, L::S.w[i]);
-        if (DDF) Sto<S>::st(gout, pix<L::Q>(r, slot), vg / nf, 0.0);
-      }
-    }
-  } else {
-    // the child's populations as the fine level's next update pulls them
-    // (every child of a coarse ghost has an explicit row), all loads first
-    C f[L::Q], g[DDF ? L::Q : 1];
-    if (ch >= 0)
-      gather_row<L, S, PRE, DDF, AAF>(fin, gin, a.xnbr, a.xstride, crow, a.vbase, ch, a.uw, a.cs2w, f, g,
-                                      mask, a.xdu);
+  const int i0 = 1 + (int)blockIdx.y * POPS;
+  int32_t sv[POPS];
 #pragma unroll
-    for (int i = 1; i < L::Q; ++i) {
-      const bool need = (mask >> i) & 1ull;
-      C v = (need && ch >= 0) ? f[i] : (C)0;
-      C vg = (DDF && need && ch >= 0) ? g[i] : (C)0;
-      v = group_sum<NCH, C>(v);
-      if (DDF) vg = group_sum<NCH, C>(vg);
-      if (lead && need) {
-        const int64_t r = SW ? L::S.opp[i] : i;
-        Sto<S>::st(fout, pix<L::Q>(r, slot), v / nf, L::S.w[i]);
-        if (DDF) Sto<S>::st(gout, pix<L::Q>(r, slot), vg / nf, 0.0);
-      }
+  for (int k = 0; k < POPS; ++k) {
+    const int i = i0 + k;
+    const bool take = i < L::Q && ((mask >> i) & 1ull) && ch >= 0;
+    sv[k] = take ? a.xnbr[(int64_t)(i - 1) * a.xstride + crow] : 0;
+  }
+  C v[POPS], vg[DDF ? POPS : 1];
+#pragma unroll
+  for (int k = 0; k < POPS; ++k) {
+    const int i = i0 + k;
+    v[k] = (C)0;
+    if (DDF) vg[k] = (C)0;
+    if (i >= L::Q || !((mask >> i) & 1ull) || ch < 0) continue;
+    int64_t idx;
+    const int64_t ri = AAF == 2 ? L::S.opp[i] : i, ro = AAF == 2 ? i : L::S.opp[i];
+    if (PRE) idx = pix<L::Q>(i, (int64_t)sv[k] >= a.vbase ? (int64_t)sv[k] : (int64_t)ch);
+    else idx = sv[k] >= 0 ? pix<L::Q>(ri, sv[k]) : pix<L::Q>(ro, ch);
+    v[k] = Sto<S>::ld(fin, idx, L::S.w[i]);
+    if (DDF) vg[k] = Sto<S>::ld(gin, idx, 0.0);
+  }
+#pragma unroll
+  for (int k = 0; k < POPS; ++k) {
+    const int i = i0 + k;
+    if (i >= L::Q) break;
+    if (!PRE && sv[k] <= -2)
+      v[k] += (C)(2.0 * L::S.w[i] * (wall_dot<L>(a.uw, -2 - sv[k], i) + noise_dot(a.xdu, a.xstride, crow, i)) /
+                  a.cs2w);
+    v[k] = group_sum<NCH, C>(v[k]);
+    if (DDF) vg[k] = group_sum<NCH, C>(vg[k]);
+    if (lead && ((mask >> i) & 1ull)) {
+      const int64_t r = SW ? L::S.opp[i] : i;
+      Sto<S>::st(fout, pix<L::Q>(r, slot), v[k] / nf, L::S.w[i]);
+      if (DDF) Sto<S>::st(gout, pix<L::Q>(r, slot), vg[k] / nf, 0.0);
     }
   }
   if (LAM) {
-    // the multipliers go with group 0 (a group's NCH lanes agree on it)
-    const bool mine = grp == 0;
-    const int64_t G = valid && mine ? a.ghost_cell[gk] : 0;
-#pragma unroll
-    for (int k = 0; k < NLAM; ++k) {
-      double v = ch >= 0 && mine ? (double)((const LamT<S> *)a.lam)[(int64_t)k * a.stride + ch] : 0.0;
+    // the multipliers go over the block rows like the populations
+    const int64_t G = valid ? a.ghost_cell[gk] : 0;
+    for (int k = (int)blockIdx.y; k < NLAM; k += (int)gridDim.y) {
+      double v = ch >= 0 ? (double)((const LamT<S> *)a.lam)[(int64_t)k * a.stride + ch] : 0.0;
       v = group_sum<NCH, double>(v);
-      if (lead && mine) ((LamT<S> *)a.lam)[(int64_t)k * a.stride + G] = (LamT<S>)(v / (double)nf);
+      if (lead) ((LamT<S> *)a.lam)[(int64_t)k * a.stride + G] = (LamT<S>)(v / (double)nf);
     }
   }
 }
@@ -1319,7 +1312,7 @@ __global__ void __launch_bounds__(BLOCK) k_coalesce(const CArgs a) {
 // the cell that pulls it from the child, as the child's own push would have
 // sent it (a wall returns it to the child's row opp(i) with the moving-wall
 // term; a population the child pulls from itself stays in its row i).
-template <class L, class S, bool DDF, bool LAM, int MODE = 0>
+template <int POPS, class L, class S, bool DDF, bool LAM, int MODE = 0>
 __global__ void __launch_bounds__(BLOCK) k_explode(const EArgs a) {
   using C = typename Sto<S>::C;
   constexpr int NCH = 1 << L::D;
@@ -1333,46 +1326,47 @@ __global__ void __launch_bounds__(BLOCK) k_explode(const EArgs a) {
   const int64_t src = MODE == 0 ? G : a.vbase + gk;
   const S *fin = (const S *)a.fin_coarse;
   S *fout = (S *)a.fout_fine;
-  S v[L::Q], vg[DDF ? L::Q : 1];
-#pragma unroll
-  for (int i = 0; i < L::Q; ++i) v[i] = fin[pix<L::Q>(i, src)];
-  if (DDF)
-#pragma unroll
-    for (int i = 0; i < L::Q; ++i) vg[i] = ((const S *)a.gin_coarse)[pix<L::Q>(i, src)];
   S *gout = (S *)a.gout_fine;
-  if constexpr (MODE == 2) {
-    const int64_t crow = a.crow[gk * NCH + (t % NCH)];
-    fout[pix<L::Q>(0, ch)] = v[0];
-    if (DDF) gout[pix<L::Q>(0, ch)] = vg[0];
+  const int64_t crow = MODE == 2 ? (int64_t)a.crow[gk * NCH + (t % NCH)] : 0;
+  const int i0 = (int)blockIdx.y * POPS;
+  S vs[POPS], vgs[DDF ? POPS : 1];
 #pragma unroll
-    for (int i = 1; i < L::Q; ++i) {
-      const int j = L::S.opp[i];
-      if (a.xnbr[(int64_t)(i - 1) * a.xstride + crow] == ch) {
-        fout[pix<L::Q>(i, ch)] = v[i];
-        if (DDF) gout[pix<L::Q>(i, ch)] = vg[i];
-      }
-      const int32_t s = a.xnbr[(int64_t)(j - 1) * a.xstride + crow];
-      if (s == ch) continue;
-      if (s >= 0) {
-        fout[pix<L::Q>(i, s)] = v[i];
-        if (DDF) gout[pix<L::Q>(i, s)] = vg[i];
-      } else {
-        C w = Sto<S>::ldv(v[i], L::S.w[i]);
-        if (s <= -2) w += (C)(2.0 * L::S.w[j] * wall_dot<L>(a.uw, -2 - s, j) / a.cs2w);
-        Sto<S>::st(fout, pix<L::Q>(j, ch), w, L::S.w[j]);
-        if (DDF) gout[pix<L::Q>(j, ch)] = vg[i];
-      }
+  for (int k = 0; k < POPS; ++k) {
+    if (i0 + k >= L::Q) break;
+    vs[k] = fin[pix<L::Q>(i0 + k, src)];
+    if (DDF) vgs[k] = ((const S *)a.gin_coarse)[pix<L::Q>(i0 + k, src)];
+  }
+#pragma unroll
+  for (int k = 0; k < POPS; ++k) {
+    const int i = i0 + k;
+    if (i >= L::Q) break;
+    const S v = vs[k], vg = DDF ? vgs[k] : S();
+    if (MODE != 2 || i == 0) {
+      const int64_t r = MODE == 1 ? L::S.opp[i] : i;
+      fout[pix<L::Q>(r, ch)] = v;
+      if (DDF) gout[pix<L::Q>(r, ch)] = vg;
+      continue;
     }
-  } else {
-#pragma unroll
-    for (int i = 0; i < L::Q; ++i) fout[pix<L::Q>(MODE == 1 ? L::S.opp[i] : i, ch)] = v[i];
-    if (DDF)
-#pragma unroll
-      for (int i = 0; i < L::Q; ++i) gout[pix<L::Q>(MODE == 1 ? L::S.opp[i] : i, ch)] = vg[i];
+    const int j = L::S.opp[i];
+    if (a.xnbr[(int64_t)(i - 1) * a.xstride + crow] == ch) {
+      fout[pix<L::Q>(i, ch)] = v;
+      if (DDF) gout[pix<L::Q>(i, ch)] = vg;
+    }
+    const int32_t s = a.xnbr[(int64_t)(j - 1) * a.xstride + crow];
+    if (s == ch) continue;
+    if (s >= 0) {
+      fout[pix<L::Q>(i, s)] = v;
+      if (DDF) gout[pix<L::Q>(i, s)] = vg;
+    } else {
+      C w = Sto<S>::ldv(v, L::S.w[i]);
+      if (s <= -2) w += (C)(2.0 * L::S.w[j] * wall_dot<L>(a.uw, -2 - s, j) / a.cs2w);
+      Sto<S>::st(fout, pix<L::Q>(j, ch), w, L::S.w[j]);
+      if (DDF) gout[pix<L::Q>(j, ch)] = vg;
+    }
   }
   if (LAM)
-#pragma unroll
-    for (int k = 0; k < NLAM; ++k) ((LamT<S> *)a.lam)[(int64_t)k * a.stride + ch] = ((LamT<S> *)a.lam)[(int64_t)k * a.stride + G];
+    for (int k = (int)blockIdx.y; k < NLAM; k += (int)gridDim.y)
+      ((LamT<S> *)a.lam)[(int64_t)k * a.stride + ch] = ((LamT<S> *)a.lam)[(int64_t)k * a.stride + G];
 }
 
 // ---------------------------------------------------------------------------
@@ -1423,7 +1417,7 @@ __device__ inline void push_value(S *f, int64_t c, const int32_t *xnbr, int64_t 
 
 // MODE 0: two buffers; 1, 2: in place, the level at an odd / even phase
 // after its step (see BArgs)
-template <class L, int COLL, class S, int MODE = 0>
+template <int POPS, class L, int COLL, class S, int MODE = 0>
 __global__ void __launch_bounds__(BLOCK) k_bcfill(const BArgs a) {
   using C = typename Sto<S>::C;
   constexpr bool DDF = COLL >= COLL_DDF_POLY;
@@ -1448,33 +1442,34 @@ __global__ void __launch_bounds__(BLOCK) k_bcfill(const BArgs a) {
 #pragma unroll
   for (int q = 0; q < 6; ++q)
     if (q == face) { fu[0] = a.fv.u[q][0]; fu[1] = a.fv.u[q][1]; fu[2] = a.fv.u[q][2]; }
-  if (kind < 0) {  // Neumann: all loads, then all stores
-    S v[L::Q], vg[DDF ? L::Q : 1];
+  if (kind < 0) {  // Neumann: the block row's populations
+    const int i0 = (int)blockIdx.y * POPS;
+    S vs[POPS], vgs[DDF ? POPS : 1];
 #pragma unroll
-    for (int i = 0; i < L::Q; ++i) v[i] = f[pix<L::Q>(srow(i), sbase)];
-    if (DDF)
+    for (int k = 0; k < POPS; ++k) {
+      if (i0 + k >= L::Q) break;
+      vs[k] = f[pix<L::Q>(srow(i0 + k), sbase)];
+      if (DDF) vgs[k] = g[pix<L::Q>(srow(i0 + k), sbase)];
+    }
 #pragma unroll
-      for (int i = 0; i < L::Q; ++i) vg[i] = g[pix<L::Q>(srow(i), sbase)];
-    if constexpr (MODE == 2) {
-      f[pix<L::Q>(0, c)] = v[0];
-      if (DDF) g[pix<L::Q>(0, c)] = vg[0];
-#pragma unroll
-      for (int i = 1; i < L::Q; ++i) {
-        push_value<L, S>(f, c, a.xnbr, a.xstride, row, i, (C)0, v[i], true, a.ph.uw, a.ph.cs2w);
-        if (DDF) push_value<L, S, true>(g, c, a.xnbr, a.xstride, row, i, (C)0, vg[i], true, a.ph.uw, 1.0);
+    for (int k = 0; k < POPS; ++k) {
+      const int i = i0 + k;
+      if (i >= L::Q) break;
+      const S v = vs[k], vg = DDF ? vgs[k] : S();
+      if (MODE == 2 && i > 0) {
+        push_value<L, S>(f, c, a.xnbr, a.xstride, row, i, (C)0, v, true, a.ph.uw, a.ph.cs2w);
+        if (DDF) push_value<L, S, true>(g, c, a.xnbr, a.xstride, row, i, (C)0, vg, true, a.ph.uw, 1.0);
+      } else {
+        f[pix<L::Q>(srow(i), c)] = v;
+        if (DDF) g[pix<L::Q>(srow(i), c)] = vg;
       }
-    } else {
-#pragma unroll
-      for (int i = 0; i < L::Q; ++i) f[pix<L::Q>(srow(i), c)] = v[i];
-      if (DDF)
-#pragma unroll
-        for (int i = 0; i < L::Q; ++i) g[pix<L::Q>(srow(i), c)] = vg[i];
     }
     if (LAM)
-#pragma unroll
-      for (int q = 0; q < NLAM; ++q) ((LamT<S> *)a.lam)[(int64_t)q * a.stride + c] = ((LamT<S> *)a.lam)[(int64_t)q * a.stride + src];
+      for (int q = (int)blockIdx.y; q < NLAM; q += (int)gridDim.y)
+        ((LamT<S> *)a.lam)[(int64_t)q * a.stride + c] = ((LamT<S> *)a.lam)[(int64_t)q * a.stride + src];
     return;
   }
+  if (blockIdx.y != 0) return;  // an equilibrium is one lane's work
   C rho = (C)frho;
   if (kind == 1) {
     rho = (C)0;
@@ -1767,41 +1762,55 @@ struct Launch {
       }
     }
   }
-  static void coalesce(const CArgs &a0, bool pre, hipStream_t s) {
-    if (a0.count <= 0) return;
-    // split the populations of a child over up to 8 lanes while the
-    // interface is too small to give every compute unit a workgroup
-    CArgs a = a0;
-    const int64_t lanes = a.count << L::D;
-    a.ngrp = (int)std::min<int64_t>(8, std::max<int64_t>(1, (256 * BLOCK) / lanes));
-    const int64_t work = lanes * a.ngrp;
-    const dim3 nb(nblocks(work));
+  // grid of an interface kernel: lanes, and block rows of POPS populations
+  template <int POPS>
+  static dim3 rows(int64_t lanes, int pops) { return dim3(nblocks(lanes), (unsigned)((pops + POPS - 1) / POPS)); }
+  template <int POPS>
+  static void coalesce_n(const CArgs &a, int64_t lanes, bool pre, hipStream_t s) {
+    const dim3 nb = rows<POPS>(lanes, L::Q - 1);
     if (a.swap) {
       // in place, coarse level at an odd phase
-      if (a.aa == 2) hipLaunchKernelGGL((k_coalesce<L, S, false, DDF, LAM, 2, true>), nb, dim3(BLOCK), 0, s, a);
-      else if (pre) hipLaunchKernelGGL((k_coalesce<L, S, true, DDF, LAM, 0, true>), nb, dim3(BLOCK), 0, s, a);
-      else hipLaunchKernelGGL((k_coalesce<L, S, false, DDF, LAM, 0, true>), nb, dim3(BLOCK), 0, s, a);
+      if (a.aa == 2) hipLaunchKernelGGL((k_coalesce<POPS, L, S, false, DDF, LAM, 2, true>), nb, dim3(BLOCK), 0, s, a);
+      else if (pre) hipLaunchKernelGGL((k_coalesce<POPS, L, S, true, DDF, LAM, 0, true>), nb, dim3(BLOCK), 0, s, a);
+      else hipLaunchKernelGGL((k_coalesce<POPS, L, S, false, DDF, LAM, 0, true>), nb, dim3(BLOCK), 0, s, a);
     } else if (a.aa == 2) {
-      hipLaunchKernelGGL((k_coalesce<L, S, false, DDF, LAM, 2>), nb, dim3(BLOCK), 0, s, a);
+      hipLaunchKernelGGL((k_coalesce<POPS, L, S, false, DDF, LAM, 2>), nb, dim3(BLOCK), 0, s, a);
     } else if (pre) {
-      hipLaunchKernelGGL((k_coalesce<L, S, true, DDF, LAM>), nb, dim3(BLOCK), 0, s, a);
+      hipLaunchKernelGGL((k_coalesce<POPS, L, S, true, DDF, LAM>), nb, dim3(BLOCK), 0, s, a);
     } else {
-      hipLaunchKernelGGL((k_coalesce<L, S, false, DDF, LAM>), nb, dim3(BLOCK), 0, s, a);
+      hipLaunchKernelGGL((k_coalesce<POPS, L, S, false, DDF, LAM>), nb, dim3(BLOCK), 0, s, a);
     }
+  }
+  static void coalesce(const CArgs &a, bool pre, hipStream_t s) {
+    if (a.count <= 0) return;
+    const int64_t lanes = a.count << L::D;
+    if (lanes < POPS_WIDE) coalesce_n<1>(a, lanes, pre, s);
+    else coalesce_n<4>(a, lanes, pre, s);
+  }
+  template <int POPS>
+  static void explode_n(const EArgs &a, int64_t lanes, hipStream_t s) {
+    const dim3 nb = rows<POPS>(lanes, L::Q);
+    if (a.mode == 1) hipLaunchKernelGGL((k_explode<POPS, L, S, DDF, LAM, 1>), nb, dim3(BLOCK), 0, s, a);
+    else if (a.mode == 2) hipLaunchKernelGGL((k_explode<POPS, L, S, DDF, LAM, 2>), nb, dim3(BLOCK), 0, s, a);
+    else hipLaunchKernelGGL((k_explode<POPS, L, S, DDF, LAM>), nb, dim3(BLOCK), 0, s, a);
   }
   static void explode(const EArgs &a, hipStream_t s) {
     if (a.count <= 0) return;
-    const dim3 nb(nblocks(a.count << L::D));
-    if (a.mode == 1) hipLaunchKernelGGL((k_explode<L, S, DDF, LAM, 1>), nb, dim3(BLOCK), 0, s, a);
-    else if (a.mode == 2) hipLaunchKernelGGL((k_explode<L, S, DDF, LAM, 2>), nb, dim3(BLOCK), 0, s, a);
-    else hipLaunchKernelGGL((k_explode<L, S, DDF, LAM>), nb, dim3(BLOCK), 0, s, a);
+    const int64_t lanes = a.count << L::D;
+    if (lanes < POPS_WIDE) explode_n<1>(a, lanes, s);
+    else explode_n<L::Q>(a, lanes, s);
+  }
+  template <int POPS>
+  static void bcfill_n(const BArgs &a, hipStream_t s) {
+    const dim3 nb = rows<POPS>(a.count, L::Q);
+    if (a.mode == 1) hipLaunchKernelGGL((k_bcfill<POPS, L, COLL, S, 1>), nb, dim3(BLOCK), 0, s, a);
+    else if (a.mode == 2) hipLaunchKernelGGL((k_bcfill<POPS, L, COLL, S, 2>), nb, dim3(BLOCK), 0, s, a);
+    else hipLaunchKernelGGL((k_bcfill<POPS, L, COLL, S>), nb, dim3(BLOCK), 0, s, a);
   }
   static void bcfill(const BArgs &a, hipStream_t s) {
     if (a.count <= 0) return;
-    const dim3 nb(nblocks(a.count));
-    if (a.mode == 1) hipLaunchKernelGGL((k_bcfill<L, COLL, S, 1>), nb, dim3(BLOCK), 0, s, a);
-    else if (a.mode == 2) hipLaunchKernelGGL((k_bcfill<L, COLL, S, 2>), nb, dim3(BLOCK), 0, s, a);
-    else hipLaunchKernelGGL((k_bcfill<L, COLL, S>), nb, dim3(BLOCK), 0, s, a);
+    if (a.count < POPS_WIDE) bcfill_n<1>(a, s);
+    else bcfill_n<4>(a, s);
   }
   static void gather(const MArgs &a, bool pre, hipStream_t s) {
     if (a.count <= 0) return;

@@ -121,7 +121,6 @@ struct CArgs {
   const int32_t *ghost_cell;
   int64_t g0, count;        // ghosts [g0, g0 + count)
   double cs2w, uw[6][3];
-  int ngrp;                 // population groups per child (set by the launcher)
   // in-place streaming: aa = 2 when the fine level's rows are swapped (odd
   // phase: the children are read as a swapped pull); swap = 1 when the
   // coarse level's are (the coalesced population i goes to row opp(i))
