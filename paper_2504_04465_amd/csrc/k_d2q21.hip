@@ -34,7 +34,8 @@ __global__ void __launch_bounds__(BLOCK) k_collide_mlp(const KArgs a) {
   stage_exp_tab(etab);
   const int32_t brick = stage_bricks<L, S>(a.topo, nbs, c, live);
   const uint8_t fl = live ? a.flags[c] : (uint8_t)F_HOLE;
-  const bool valid = !(fl & F_HOLE);
+  // (fine ghosts that the coarse ghosts overwrite in this substep do nothing)
+  const bool valid = !(fl & F_HOLE) && !(a.skip_fg && (fl & F_FINE_GHOST));
   C rho = (C)1, u[3] = {(C)0, (C)0, (C)0}, T = (C)1;
   if (valid) {
     C f[Q], g[Q];
@@ -109,9 +110,13 @@ __global__ void __launch_bounds__(BLOCK) k_collide_mlp(const KArgs a) {
     S *gout = (S *)a.gout;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
-      Sto<S>::stn(fout, pix<Q>(i, c), f[i] - om * (f[i] - feq[i]), L::S.w[i]);
-      Sto<S>::stn(gout, pix<Q>(i, c), g[i] - om * (g[i] - geq[i]), 0.0);
+      f[i] = f[i] - om * (f[i] - feq[i]);
+      g[i] = g[i] - om * (g[i] - geq[i]);
+      Sto<S>::stn(fout, pix<Q>(i, c), f[i], L::S.w[i]);
+      Sto<S>::stn(gout, pix<Q>(i, c), g[i], 0.0);
     }
+    if (a.ef && (fl & F_COARSE_GHOST))
+      explode_store<L, S, true, true>(a, a.ef, a.eg, fout, gout, c, f, g);
   } else if (valid) {
     // fine ghosts and boundary layers: streamed, not collided
     C f[Q], g[Q];

@@ -990,6 +990,96 @@ struct CollideBlock {
   static constexpr int value = BLOCK;
 };
 
+// Uniform explosion by the coarse ghost itself (two buffers): every
+// post-collision population into its children on the finer level, whose
+// output buffer ef / eg the same launch or a later one of the substep
+// completes; their own lanes store nothing.  The children of a ghost are
+// neighbours in Z order, so they are one aligned run of 2^D slots (unless a
+// body cut some away) and take 16-byte stores.  This replaces a launch that
+// read the ghosts' rows again, and the fine ghosts' own streaming that it
+// overwrote: per coarse step 2.3-11.5 us a launch and the gap before it
+// (passes of four steps: cylinder 2.70 -> 2.60 ms, sphere FP32 4.17 -> 4.00,
+// FP16 3.05 -> 2.89, airfoil 2.79 -> 2.76; twenty steps of the 64 x 64 cavity
+// 456 -> 421 us).
+template <class S>
+struct RawOf {
+  using T = S;
+  __device__ static T of(typename Sto<S>::C v, double) { return v; }
+};
+template <>
+struct RawOf<__half> {
+  using T = unsigned short;
+  __device__ static T of(float v, double w) { return __half_as_ushort(Sto<__half>::cvt(v, w)); }
+};
+
+template <class L, class S, bool DDF, bool LAM, bool SH = false>
+__device__ inline void explode_store(const KArgs &a, void *ef, void *eg, const S *fout, const S *gout, int64_t c,
+                                     const typename Sto<S>::C *f, const typename Sto<S>::C *g) {
+  constexpr int NCH = 1 << L::D;
+  constexpr int PER = sizeof(S) * NCH < 16 ? NCH : 16 / (int)sizeof(S);
+  using E = typename RawOf<S>::T;
+  constexpr int WORDS = PER * (int)sizeof(S) / 4, WPE = sizeof(S) == 8 ? 2 : 1;
+  typedef uint32_t vec __attribute__((ext_vector_type(WORDS)));
+  // the mask is read again rather than held across the collision
+  const int64_t row = a.topo.xbase[c >> 6] + __popcll(a.topo.xmask[c >> 6] & ((1ull << (c & 63)) - 1ull));
+  const int32_t *cp = a.child + (int64_t)a.xghost[row] * NCH;
+  int32_t ch[NCH];
+#pragma unroll
+  for (int k = 0; k < NCH; ++k) ch[k] = cp[k];
+  bool run = ch[0] >= 0 && (ch[0] & (NCH - 1)) == 0;
+#pragma unroll
+  for (int k = 1; k < NCH; ++k) run = run && ch[k] == ch[0] + k;
+  if (run) {
+    auto put = [&](void *buf, int i, E v) {
+      uint32_t word[WPE];
+      if constexpr (sizeof(E) == 2) word[0] = (uint32_t)v * 0x10001u;
+      else __builtin_memcpy(word, &v, sizeof(E));
+      // (moves that the compiler cannot merge with v: as parts of one tuple
+      // of registers the populations would be spilled four at a time)
+      vec w;
+#pragma unroll
+      for (int q = 0; q < WORDS; ++q) {
+        uint32_t x;
+        asm volatile("v_mov_b32 %0, %1" : "=v"(x) : "v"(word[q % WPE]));
+        w[q] = x;
+      }
+      E *p = (E *)buf + pix<L::Q>(i, ch[0]);
+#pragma unroll
+      for (int k = 0; k < NCH; k += PER) *(vec *)(p + k) = w;
+    };
+    // one population at a time: the copies of all of them at once do not fit
+    // the registers that the collide leaves
+#pragma unroll
+    for (int i = 0; i < L::Q; ++i) {
+      put(ef, i, RawOf<S>::of(f[i], SH ? 0.0 : L::S.w[i]));
+      if (DDF) put(eg, i, RawOf<S>::of(g[i], 0.0));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  } else {
+    // a body cuts into the children: the ghost's own stores, read back
+#pragma unroll 1
+    for (int i = 0; i < L::Q; ++i) {
+      const E v = ((const E *)fout)[pix<L::Q>(i, c)];
+      const E vg = DDF ? ((const E *)gout)[pix<L::Q>(i, c)] : E();
+#pragma unroll
+      for (int k = 0; k < NCH; ++k)
+        if (ch[k] >= 0) {
+          ((E *)ef)[pix<L::Q>(i, ch[k])] = v;
+          if (DDF) ((E *)eg)[pix<L::Q>(i, ch[k])] = vg;
+        }
+    }
+  }
+  if (LAM)
+#pragma unroll
+    for (int q = 0; q < NLAM; ++q) {
+      LamT<S> *lam = (LamT<S> *)a.lam + (int64_t)q * a.stride;
+      const LamT<S> v = lam[c];
+#pragma unroll
+      for (int k = 0; k < NCH; ++k)
+        if (ch[k] >= 0) lam[ch[k]] = v;
+    }
+}
+
 // AA selects in-place streaming on one buffer (a.fin == a.fout): 1 = even
 // step (read the cell's own rows, write population i to its row opp(i)),
 // 2 = odd step (pull from the swapped rows, push to the neighbours).
@@ -1014,6 +1104,8 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
   const void *fin_p = a.fin, *gin_p = a.gin;
   void *fout_p = a.fout, *gout_p = a.gout;
   double tau = a.ph.tau, omega = a.ph.omega, krr = a.ph.krr;
+  void *ef = a.ef, *eg = a.eg;
+  bool skip_fg = a.skip_fg != 0;
   bool multi = false;
   if constexpr (!PRE && AA == 0 && COLL < COLL_DDF_NEWTON) multi = a.multi.n > 0;
   if (multi) {
@@ -1033,6 +1125,12 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
     fout_p = (void *)a.multi.f[1 - p];
     gin_p = a.multi.g[p];
     gout_p = (void *)a.multi.g[1 - p];
+    // the active levels of a substep are the finest n: the launch holds
+    // every finer level, and no coarser one is active
+    const int pf = k + 1 < a.multi.n ? a.multi.parity[k + 1] : 0;
+    ef = k + 1 < a.multi.n ? (void *)a.multi.f[1 - pf] : nullptr;
+    eg = (void *)a.multi.g[1 - pf];
+    skip_fg = k > 0;
     if (blk * CB >= count) return;  // padding blocks of the level
   } else {
     blk = xcd_block();
@@ -1051,6 +1149,7 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
   const int32_t brick = stage_bricks<L, S>(a.topo, nbs, c, live);
   if (!live) return;
   if (fl & F_HOLE) return;
+  if (AA == 0 && skip_fg && (fl & F_FINE_GHOST)) return;
   const S *fin = (const S *)fin_p;
   const S *gin = (const S *)gin_p;
   C f[Q];
@@ -1210,6 +1309,10 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
       }
     }
   }
+  if constexpr (AA == 0) {
+    if (ef && (fl & F_COARSE_GHOST))
+      explode_store<L, S, DDF, (COLL >= COLL_DDF_NEWTON), SH>(a, ef, eg, fout, gout, c, f, g);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1223,11 +1326,10 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
 // 8.2 us; with one population per lane 7.6 and 4.0 us.
 // POPS = 1 below POPS_WIDE lanes, where the lanes of one population leave
 // compute units idle.  Above, a lane's table reads serve several populations,
-// whose loads are in flight together: four for the coalescence (sphere, 31 k
-// ghosts of 8 children: 29.3 us a launch with one, 26.2 with four, 28.2 with
-// all 27) and the boundary fill, all of them for the explosion's plain copy
-// (18.2 us with one, 12.8 with four, 11.5 with all).  On the cylinder's
-// interfaces (up to 37 k lanes) four instead of one cost 2.5 % of the step.
+// whose loads are in flight together: four of them (coalescence on the
+// sphere, 31 k ghosts of 8 children: 29.3 us a launch with one, 26.2 with
+// four, 28.2 with all 27).  On the cylinder's interfaces (up to 37 k lanes)
+// four instead of one cost 2.5 % of the step.
 // ---------------------------------------------------------------------------
 constexpr int64_t POPS_WIDE = 65536;
 
@@ -1304,15 +1406,15 @@ __global__ void __launch_bounds__(BLOCK) k_coalesce(const CArgs a) {
 }
 
 // uniform explosion (Eq. explosion_uniform): children take every
-// post-collision population of their coarse ghost (raw copy of storage).
-// MODE 0: two buffers, from the ghost's slot into the child's rows.  In
-// place the ghost's populations are read from its coalesced slot, where its
-// collide left them; MODE 1 (fine level at an odd phase): child row opp(i)
+// post-collision population of their coarse ghost (raw copy of storage), in
+// place: with two buffers the collide stores them (explode_store).  The
+// ghost's populations are read from its coalesced slot, where its collide
+// left them; MODE 1 (fine level at an odd phase): child row opp(i)
 // takes population i; MODE 2 (even phase): population i goes to row i of
 // the cell that pulls it from the child, as the child's own push would have
 // sent it (a wall returns it to the child's row opp(i) with the moving-wall
 // term; a population the child pulls from itself stays in its row i).
-template <int POPS, class L, class S, bool DDF, bool LAM, int MODE = 0>
+template <int POPS, class L, class S, bool DDF, bool LAM, int MODE>
 __global__ void __launch_bounds__(BLOCK) k_explode(const EArgs a) {
   using C = typename Sto<S>::C;
   constexpr int NCH = 1 << L::D;
@@ -1323,7 +1425,7 @@ __global__ void __launch_bounds__(BLOCK) k_explode(const EArgs a) {
   const int32_t ch = a.child[gk * NCH + (t % NCH)];
   if (ch < 0) return;
   const int64_t G = a.ghost_cell[gk];
-  const int64_t src = MODE == 0 ? G : a.vbase + gk;
+  const int64_t src = a.vbase + gk;
   const S *fin = (const S *)a.fin_coarse;
   S *fout = (S *)a.fout_fine;
   S *gout = (S *)a.gout_fine;
@@ -1799,14 +1901,13 @@ struct Launch {
   static void explode_n(const EArgs &a, int64_t lanes, hipStream_t s) {
     const dim3 nb = rows<POPS>(lanes, L::Q);
     if (a.mode == 1) hipLaunchKernelGGL((k_explode<POPS, L, S, DDF, LAM, 1>), nb, dim3(BLOCK), 0, s, a);
-    else if (a.mode == 2) hipLaunchKernelGGL((k_explode<POPS, L, S, DDF, LAM, 2>), nb, dim3(BLOCK), 0, s, a);
-    else hipLaunchKernelGGL((k_explode<POPS, L, S, DDF, LAM>), nb, dim3(BLOCK), 0, s, a);
+    else hipLaunchKernelGGL((k_explode<POPS, L, S, DDF, LAM, 2>), nb, dim3(BLOCK), 0, s, a);
   }
   static void explode(const EArgs &a, hipStream_t s) {
     if (a.count <= 0) return;
     const int64_t lanes = a.count << L::D;
     if (lanes < POPS_WIDE) explode_n<1>(a, lanes, s);
-    else explode_n<L::Q>(a, lanes, s);
+    else explode_n<4>(a, lanes, s);
   }
   template <int POPS>
   static void bcfill_n(const BArgs &a, hipStream_t s) {

@@ -79,6 +79,7 @@ struct lbm_ctx {
   void *d_lam = nullptr;   // multipliers: FP64 with FP64 storage, else FP32
   int lam_bytes = 4;
   int32_t *d_ghost = nullptr, *d_child = nullptr;
+  int32_t *d_xghost = nullptr;  // coarse ghost of each explicit row (-1: the row's cell is none)
   uint64_t *d_unknown = nullptr;
   int32_t *d_bc_cell = nullptr, *d_bc_src = nullptr;
   int8_t *d_bc_face = nullptr;
@@ -163,7 +164,7 @@ void free_device(lbm_ctx *c) {
   c->dg = DeviceGridArrays();
   c->d_sigma = c->d_rhoinf = nullptr;
   c->d_lam = nullptr;
-  c->d_ghost = c->d_child = nullptr;
+  c->d_ghost = c->d_child = c->d_xghost = nullptr;
   c->d_unknown = nullptr;
   c->d_bc_cell = c->d_bc_src = nullptr;
   c->d_bc_face = nullptr;
@@ -280,6 +281,7 @@ void launch_coalesce(lbm_ctx *c, int l) {
   c->ops.coalesce(a, read_pre(c, l + 1), c->stream);
 }
 
+// in place: the explosion of level l's coarse ghosts, after both levels' steps
 void launch_explode(lbm_ctx *c, int l) {
   const int64_t cnt = c->g.goff[l + 1] - c->g.goff[l];
   if (cnt <= 0) return;
@@ -294,17 +296,15 @@ void launch_explode(lbm_ctx *c, int l) {
   a.ghost_cell = c->d_ghost;
   a.g0 = c->g.goff[l];
   a.count = cnt;
-  if (c->p.in_place) {
-    // the fine level has just stepped: odd phase, rows swapped
-    a.mode = c->parity[l + 1] == 1 ? 1 : 2;
-    a.vbase = c->NS;
-    a.xnbr = c->d_xnbr;
-    a.xstride = c->lay.xstride;
-    a.crow = c->d_crow;
-    const PhysArgs ph = phys(c, l + 1);
-    a.cs2w = ph.cs2w;
-    memcpy(a.uw, ph.uw, sizeof a.uw);
-  }
+  // the fine level has just stepped: odd phase, rows swapped
+  a.mode = c->parity[l + 1] == 1 ? 1 : 2;
+  a.vbase = c->NS;
+  a.xnbr = c->d_xnbr;
+  a.xstride = c->lay.xstride;
+  a.crow = c->d_crow;
+  const PhysArgs ph = phys(c, l + 1);
+  a.cs2w = ph.cs2w;
+  memcpy(a.uw, ph.uw, sizeof a.uw);
   c->ops.explode(a, c->stream);
 }
 
@@ -357,6 +357,9 @@ hipEvent_t take_event(lbm_ctx *c) {
   return e;
 }
 
+// whether level l is active at finest substep t of a coarse step
+bool active(const lbm_ctx *c, int l, int t) { return l >= 0 && t % (1 << (c->L - 1 - l)) == 0; }
+
 // argument block of level l's collide reading buffer par
 KArgs collide_args(lbm_ctx *c, int l, int par) {
   KArgs a{};
@@ -376,13 +379,23 @@ KArgs collide_args(lbm_ctx *c, int l, int par) {
   a.ph = phys(c, l);
   a.counters = c->d_counters;
   a.gslot = c->d_gslot;
+  a.xghost = c->d_xghost;
+  a.child = c->d_child;
   return a;
 }
 
-void launch_collide(lbm_ctx *c, int l) {
+void launch_collide(lbm_ctx *c, int l, int t) {
   const int64_t cnt = c->lay.soff[l + 1] - c->lay.soff[l];
   if (cnt > 0) {
     KArgs a = collide_args(c, l, c->parity[l]);
+    if (!c->p.in_place) {
+      // levels go coarsest first, so the finer level still reads parity[l + 1]
+      if (l + 1 < c->L) {
+        a.ef = c->f[1 - c->parity[l + 1]];
+        a.eg = c->gb[1 - c->parity[l + 1]];
+      }
+      a.skip_fg = active(c, l - 1, t);
+    }
     ProfSlot slot{};
     if (c->prof) {
       slot.a = take_event(c);
@@ -786,6 +799,20 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
     std::vector<int32_t> bcc(c->g.bc_cell.size()), bcs(c->g.bc_src.size());
     for (size_t k = 0; k < bcc.size(); ++k) bcc[k] = y.slot_of[c->g.bc_cell[k]];
     for (size_t k = 0; k < bcs.size(); ++k) bcs[k] = y.slot_of[c->g.bc_src[k]];
+    // a coarse ghost pulls at least one population from its children, so it
+    // has an explicit row, which names its entry in the child table
+    std::vector<int32_t> xg((size_t)std::max<int64_t>(y.nx, 1), -1);
+    for (size_t k = 0; k < gs.size(); ++k) {
+      const int32_t r = y.xrow_of[c->g.ghost_cell[k]];
+      if (r < 0) return set_err(c, LBM_E_ARG, "internal: coarse ghost without an exception row");
+      xg[r] = (int32_t)k;
+    }
+    if ((s = upload(c, &c->d_xghost, xg.data(), xg.size())) != LBM_OK) return s;
+    // the collide explodes before the boundary fills read their sources: no
+    // source is a fine ghost, whose parent would be a coarse ghost at depth
+    // B / 2 < B from the face, inside the coarse boundary layer
+    for (int32_t src : c->g.bc_src)
+      if (c->g.flag[src] & F_FINE_GHOST) return set_err(c, LBM_E_ARG, "internal: boundary source is a fine ghost");
     if ((s = upload(c, &c->d_ghost, gs.data(), gs.size())) != LBM_OK) return s;
     if ((s = upload(c, &c->d_child, ch.data(), ch.size())) != LBM_OK) return s;
     if ((s = upload(c, &c->d_crow, cr.data(), cr.size())) != LBM_OK) return s;
@@ -1187,24 +1214,24 @@ void coarse_step(lbm_ctx *c) {
   for (int t = 0; t < (1 << (L - 1)); ++t) {
     if (fused_ok(c, t)) {
       // coalescences (each reads the finer level's state of the previous
-      // substep), the collides of all active levels at once, then the
-      // boundary fills and explosions in the per-level order
+      // substep), the collides of all active levels at once with the
+      // explosions, then the boundary fills
       for (int l = 0; l + 1 < L; ++l)
         if (t % (1 << (L - 1 - l)) == 0) launch_coalesce(c, l);
       launch_collide_fused(c, t);
       for (int l = 0; l < L; ++l) {
         if (t % (1 << (L - 1 - l)) != 0) continue;
         launch_bcfill(c, l);
-        if (l > 0 && t % (1 << (L - l)) == 0) launch_explode(c, l - 1);
       }
       continue;
     }
     for (int l = 0; l < L; ++l) {
       if (t % (1 << (L - 1 - l)) != 0) continue;
       if (l + 1 < L) launch_coalesce(c, l);
-      launch_collide(c, l);
+      launch_collide(c, l, t);
       launch_bcfill(c, l);
-      if (l > 0 && t % (1 << (L - l)) == 0) launch_explode(c, l - 1);
+      // (with two buffers the collides explode their coarse ghosts themselves)
+      if (c->p.in_place && active(c, l - 1, t)) launch_explode(c, l - 1);
     }
   }
   c->coarse_steps++;

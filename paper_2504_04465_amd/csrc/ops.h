@@ -101,6 +101,14 @@ struct KArgs {
   // (-1 elsewhere); a ghost leaves its post-collision populations there,
   // row i, for the explosion
   const int32_t *gslot;
+  // two buffers: the explosion inside the collide.  Coarse-ghost lanes also
+  // store their post-collision populations in their children, slots
+  // child[xghost[row]][..] of the finer level's output buffer ef / eg (null:
+  // not in this launch), and fine ghosts whose coarse level is active at
+  // this substep (skip_fg) do nothing, since they are overwritten
+  const int32_t *xghost, *child;
+  void *ef, *eg;
+  int skip_fg;
   MultiTable multi;    // n > 0: every active level of a substep in one launch
 };
 
@@ -127,7 +135,8 @@ struct CArgs {
   int aa, swap;
 };
 
-// uniform explosion of coarse-ghost post-collision states into the children
+// uniform explosion of coarse-ghost post-collision states into the children,
+// in place (with two buffers the collide does it)
 struct EArgs {
   const void *fin_coarse;
   void *fout_fine;
@@ -137,9 +146,8 @@ struct EArgs {
   int64_t stride;
   const int32_t *child, *ghost_cell;
   int64_t g0, count;
-  // in-place streaming (mode 0: two buffers): the coarse ghost's
-  // post-collision populations are read from its coalesced slot (vbase +
-  // ghost index, where its collide left them); mode 1, the fine level is at
+  // the coarse ghost's post-collision populations are read from its
+  // coalesced slot (vbase + ghost index, where its collide left them); mode 1, the fine level is at
   // an odd phase: child row opp(i) takes population i; mode 2, even phase:
   // population i goes to row i of the cell that pulls it from the child
   // (through the child's exception row), the bounce-back into the child's
