@@ -162,8 +162,10 @@ lbm_status lbm_grid_build(lbm_ctx *ctx, int dim, const int32_t ext_coarse[3],
  * layout (Secs. 4.3-4.4; Sec. 8 names the host-side tree construction as
  * the cost of remeshing): on = 1 (the default) builds them on the GPU,
  * every rule of the construction applied per cell in parallel (Z order by
- * a radix sort of Morton keys, lists by prefix sums), and copies the result
- * into the context's host copy; on = 0 builds them on the host.  Both give
+ * a radix sort of Morton keys, lists by prefix sums), and keeps the result
+ * there: readers of the tables (lbm_grid_export, lbm_layout_export,
+ * lbm_set_inflow_noise, in-place builds) copy them to the host the first
+ * time they need them; on = 0 builds them on the host.  Both give
  * the same grid value for value and the same errors.  Host-only contexts
  * always build on the host.  Takes effect at the next build.  Errors:
  * LBM_E_ARG (null context). */

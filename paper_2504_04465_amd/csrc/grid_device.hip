@@ -24,7 +24,7 @@ namespace {
 enum : uint8_t { S_INR = 1, S_REF = 2, S_STRIP = 4, S_PRE = 8, S_EXIST = 16 };
 enum : int {
   E_NEST = 1, E_IFACE = 2, E_CUT = 4, E_BOTH = 8, E_OVERLAP = 16, E_NOSRC = 32, E_SRCBC = 64, E_ORPHAN = 128,
-  E_BRICK = 256
+  E_BRICK = 256, E_ROWS = 512, E_BCGHOST = 1024
 };
 
 constexpr int TPB = 256;
@@ -586,6 +586,71 @@ __global__ void k_xrows(int64_t n, int Qm, int64_t xstride, int64_t vbase, const
   }
 }
 
+// ---- lists over slots and rows -----------------------------------------------------
+// out[k] = map[list[k]], -1 kept
+__global__ void k_mapped(int64_t m, const int32_t *list, const int32_t *map, int32_t *out) {
+  GRID_STRIDE(k, m) out[k] = list[k] < 0 ? -1 : map[list[k]];
+}
+
+// explicit rows of the children of coarse ghosts and of the ghosts
+// themselves; each must have one
+__global__ void k_ghost_rows(int64_t ng, int nch, const int32_t *ghost, const int32_t *child, const int32_t *xrow_of,
+                             int32_t *child_row, int32_t *row_ghost, int *err) {
+  GRID_STRIDE(k, ng) {
+    for (int o = 0; o < nch; ++o) {
+      const int32_t v = child[k * nch + o];
+      const int32_t r = v < 0 ? 0 : xrow_of[v];
+      if (r < 0) atomicOr(err, E_ROWS);
+      child_row[k * nch + o] = r;
+    }
+    const int32_t r = xrow_of[ghost[k]];
+    if (r < 0) atomicOr(err, E_ROWS);
+    else row_ghost[r] = (int32_t)k;
+  }
+}
+
+__global__ void k_bc_ghost(int64_t m, const int32_t *src, const uint8_t *flag, int *err) {
+  GRID_STRIDE(k, m) if (flag[src[k]] & F_FINE_GHOST) atomicOr(err, E_BCGHOST);
+}
+
+__global__ void k_slot_values(int64_t n, const double *v, const int32_t *slot_of, double *out) {
+  GRID_STRIDE(c, n) out[slot_of[c]] = v[c];
+}
+
+// the populations of every explicit row that the brick arithmetic would
+// pull from the same slot (regular_pulls)
+__global__ void k_xreg(DLat lat, int64_t nbrk, int D, int sh, int nbp, int64_t xstride,
+                       const unsigned long long *xmask, const int32_t *xbase, const int32_t *nbrick,
+                       const int32_t *xnbr, uint64_t *xreg) {
+  const int bs = 1 << sh;
+  GRID_STRIDE(s, nbrk * 64) {
+    const int64_t b = s >> 6;
+    const int lane = (int)(s & 63);
+    const unsigned long long m = xmask[b];
+    if (!((m >> lane) & 1ull)) continue;
+    const int64_t row = xbase[b] + __popcll(m & ((1ull << lane) - 1ull));
+    int lc[3] = {0, 0, 0};
+    for (int k = 0; k < sh; ++k)
+      for (int a = 0; a < D; ++a) lc[a] |= ((lane >> (D * k + a)) & 1) << k;
+    uint64_t bits = 0;
+    for (int i = 1; i < lat.Q; ++i) {
+      int dir = 0, pw = 1, q[3] = {0, 0, 0};
+      for (int a = 0; a < D; ++a) {
+        const int64_t p = lc[a] - lat.c[i][a];
+        const int64_t w = floordiv_d(p, bs);
+        q[a] = (int)(p - w * bs);
+        dir += (int)(w + 1) * pw;
+        pw *= 3;
+      }
+      const int32_t nb = nbrick[b * nbp + dir];
+      if (nb >= 0 && (int64_t)xnbr[(int64_t)(i - 1) * xstride + row] ==
+                         (int64_t)nb * 64 + brick_local_d(D, sh, q[0], q[1], q[2]))
+        bits |= 1ull << i;
+    }
+    xreg[row] = bits;
+  }
+}
+
 // ---- remesh sources ----------------------------------------------------------------
 // dense index of the old flow cells of one level over their bounding box
 struct DFlow {
@@ -1057,9 +1122,9 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
     hipLaunchKernelGGL(k_flag_nonneg, dim3(grid_for(n)), dim3(T), 0, st, n, src_all, fl);
     DEV_TRY(exclusive_sum(pool, fl, pos, n, st, &nbc));
     DEV_TRY(level_offsets(pos, nbc, g.boff));
-    bc_cell = pool.take<int32_t>(nbc);
-    bc_src = pool.take<int32_t>(nbc);
-    bc_face = pool.take<int8_t>(nbc);
+    bc_cell = (int32_t *)kept(sizeof(int32_t) * nbc);
+    bc_src = (int32_t *)kept(sizeof(int32_t) * nbc);
+    bc_face = (int8_t *)kept(nbc);
     DEV_MEM(bc_cell);
     DEV_MEM(bc_src);
     DEV_MEM(bc_face);
@@ -1094,9 +1159,9 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
   } else {
     for (int l = 0; l <= L; ++l) g.goff[l] = 0;
   }
-  ghost = pool.take<int32_t>(ng);
-  child = pool.take<int32_t>((size_t)ng * NCH);
-  unknown = pool.take<uint64_t>(ng);
+  ghost = (int32_t *)kept(sizeof(int32_t) * ng);
+  child = (int32_t *)kept(sizeof(int32_t) * ng * NCH);
+  unknown = (uint64_t *)kept(sizeof(uint64_t) * ng);
   DEV_MEM(ghost);
   DEV_MEM(child);
   DEV_MEM(unknown);
@@ -1165,8 +1230,8 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
   y.nslot = slots;
   if (slots >= INT32_MAX / 2) return fail(err, -1, "grid too large for 32-bit slot indices");
   const int64_t nbrk = slots / 64;
-  int32_t *cell_of = pool.take<int32_t>(slots);
-  int32_t *nbrick = pool.take<int32_t>((size_t)nbrk * y.nbp);
+  int32_t *cell_of = (int32_t *)kept(sizeof(int32_t) * slots);
+  int32_t *nbrick = (int32_t *)kept(sizeof(int32_t) * nbrk * y.nbp);
   DEV_MEM(cell_of);
   DEV_MEM(nbrick);
   DEV_TRY(hipMemsetAsync(cell_of, 0xff, sizeof(int32_t) * std::max<int64_t>(slots, 1), st));
@@ -1185,8 +1250,8 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
   }
   // exception rows
   uint8_t *special = pool.take<uint8_t>(n);
-  unsigned long long *xmask = pool.take<unsigned long long>(nbrk);
-  int32_t *pc = pool.take<int32_t>(nbrk), *xbase = pool.take<int32_t>(nbrk);
+  unsigned long long *xmask = (unsigned long long *)kept(sizeof(unsigned long long) * nbrk);
+  int32_t *pc = pool.take<int32_t>(nbrk), *xbase = (int32_t *)kept(sizeof(int32_t) * nbrk);
   int32_t *gidx = pool.take<int32_t>(n), *xrow_of = pool.take<int32_t>(n);
   DEV_MEM(special);
   DEV_MEM(xmask);
@@ -1212,7 +1277,7 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
   }
   y.nx = rows;
   y.xstride = std::max<int64_t>(64, ((rows + 63) / 64) * 64);
-  int32_t *xnbr = pool.take<int32_t>((size_t)Qm * y.xstride);
+  int32_t *xnbr = (int32_t *)kept(sizeof(int32_t) * Qm * y.xstride);
   DEV_MEM(xnbr);
   DEV_TRY(hipMemsetAsync(xnbr, 0xff, sizeof(int32_t) * (size_t)Qm * y.xstride, st));
   if (ng > 0) hipLaunchKernelGGL(k_gidx, dim3(grid_for(ng)), dim3(T), 0, st, ng, ghost, gidx);
@@ -1221,11 +1286,78 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
                        xmask, xbase, nbr, gidx, xrow_of, xnbr);
   DEV_TRY(hipGetLastError());
 
-  // ---- back to the host structures ----
-  if (!keep) {
-    DEV_TRY(down(g.xyz, xyz, 3 * n, st));
-    DEV_TRY(down(g.nbr, nbr, (size_t)Qm * n, st));
+  if (keep) {
+    // ---- the lists over slots, left on the device ----
+    keep->ghost = ghost;
+    keep->child = child;
+    keep->unknown = unknown;
+    keep->bc_cell = bc_cell;
+    keep->bc_src = bc_src;
+    keep->bc_face = bc_face;
+    keep->ng = ng;
+    keep->nbc = nbc;
+    keep->nch = NCH;
+    keep->cell_of = cell_of;
+    keep->nbrick = nbrick;
+    keep->xmask = xmask;
+    keep->xbase = xbase;
+    keep->xnbr = xnbr;
+    keep->nslot = slots;
+    keep->xstride = y.xstride;
+    keep->nbp = y.nbp;
+    auto mapped = [&](int64_t m, const int32_t *list) -> int32_t * {
+      int32_t *o = (int32_t *)kept(sizeof(int32_t) * m);
+      if (o && m > 0) hipLaunchKernelGGL(k_mapped, dim3(grid_for(m)), dim3(T), 0, st, m, list, slot_of, o);
+      return o;
+    };
+    DEV_MEM(keep->ghost_slot = mapped(ng, ghost));
+    DEV_MEM(keep->child_slot = mapped(ng * NCH, child));
+    DEV_MEM(keep->bc_cell_slot = mapped(nbc, bc_cell));
+    DEV_MEM(keep->bc_src_slot = mapped(nbc, bc_src));
+    DEV_MEM(keep->child_row = (int32_t *)kept(sizeof(int32_t) * ng * NCH));
+    DEV_MEM(keep->row_ghost = (int32_t *)kept(sizeof(int32_t) * std::max<int64_t>(rows, 1)));
+    DEV_MEM(keep->xreg = (uint64_t *)kept(sizeof(uint64_t) * std::max<int64_t>(rows, 1)));
+    DEV_TRY(hipMemsetAsync(keep->row_ghost, 0xff, sizeof(int32_t) * std::max<int64_t>(rows, 1), st));
+    if (ng > 0)
+      hipLaunchKernelGGL(k_ghost_rows, dim3(grid_for(ng)), dim3(T), 0, st, ng, NCH, ghost, child, xrow_of,
+                         keep->child_row, keep->row_ghost, derr);
+    if (nbc > 0) hipLaunchKernelGGL(k_bc_ghost, dim3(grid_for(nbc)), dim3(T), 0, st, nbc, bc_src, flag, derr);
+    if (rows > 0)
+      hipLaunchKernelGGL(k_xreg, dim3(grid_for(slots)), dim3(T), 0, st, dl, nbrk, D, sh, y.nbp, y.xstride, xmask,
+                         xbase, nbrick, xnbr, keep->xreg);
+    // explicit rows per level: the exclusive sum at its first brick
+    std::vector<int32_t> xb0(L + 1, (int32_t)rows);
+    for (int l = 0; l < L; ++l)
+      if (y.soff[l] < slots)
+        DEV_TRY(hipMemcpyAsync(&xb0[l], xbase + y.soff[l] / 64, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+    int64_t nsp[9] = {0};
+    if (any_sponge) {
+      DEV_MEM(keep->sigma = (double *)kept(sizeof(double) * slots));
+      DEV_MEM(keep->rho_inf = (double *)kept(sizeof(double) * slots));
+      DEV_TRY(hipMemsetAsync(keep->sigma, 0, sizeof(double) * std::max<int64_t>(slots, 1), st));
+      DEV_TRY(hipMemsetAsync(keep->rho_inf, 0, sizeof(double) * std::max<int64_t>(slots, 1), st));
+      if (n > 0) {
+        hipLaunchKernelGGL(k_slot_values, dim3(grid_for(n)), dim3(T), 0, st, n, sigma, slot_of, keep->sigma);
+        hipLaunchKernelGGL(k_slot_values, dim3(grid_for(n)), dim3(T), 0, st, n, rho_inf, slot_of, keep->rho_inf);
+        hipLaunchKernelGGL(k_flag_bits, dim3(grid_for(n)), dim3(T), 0, st, n, flag, (uint8_t)F_SPONGE, fl);
+        int64_t all = 0;
+        DEV_TRY(exclusive_sum(pool, fl, pos, n, st, &all));
+        DEV_TRY(level_offsets(pos, all, nsp));
+      }
+    }
+    int h = 0;
+    DEV_TRY(errors(&h));  // (waits for the copies above)
+    if (h & E_ROWS) return fail(err, -1, "internal: coarse ghost or child without an exception row");
+    if (h & E_BCGHOST) return fail(err, -1, "internal: boundary source is a fine ghost");
+    for (int l = 0; l < L; ++l) {
+      keep->rows[l] = xb0[l + 1] - xb0[l];
+      keep->sponge[l] = nsp[l + 1] - nsp[l];
+    }
+    return 0;
   }
+  // ---- back to the host structures ----
+  DEV_TRY(down(g.xyz, xyz, 3 * n, st));
+  DEV_TRY(down(g.nbr, nbr, (size_t)Qm * n, st));
   DEV_TRY(down(g.lev, lev, n, st));
   DEV_TRY(down(g.flag, flag, n, st));
   DEV_TRY(down(g.bc_src_all, src_all, n, st));
@@ -1252,17 +1384,41 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
   return 0;
 }
 
-int fetch_host_mirror(const DeviceGridArrays &dg, HostGrid *g, hipStream_t st, std::string *err) {
-  bool any = false;
-  if (dg.xyz && g->xyz.empty()) {
-    DEV_TRY(down(g->xyz, dg.xyz, 3 * dg.n, st));
-    any = true;
+int fetch_host_grid(const DeviceGridArrays &dg, HostGrid *g, hipStream_t st, std::string *err) {
+  if (!dg.xyz || !g->xyz.empty() || dg.n == 0) return 0;
+  DEV_TRY(down(g->xyz, dg.xyz, 3 * dg.n, st));
+  DEV_TRY(down(g->lev, dg.lev, dg.n, st));
+  DEV_TRY(down(g->flag, dg.flag, dg.n, st));
+  DEV_TRY(down(g->ghost_cell, dg.ghost, dg.ng, st));
+  DEV_TRY(down(g->child, dg.child, (size_t)dg.ng * dg.nch, st));
+  DEV_TRY(down(g->unknown, dg.unknown, dg.ng, st));
+  DEV_TRY(down(g->bc_cell, dg.bc_cell, dg.nbc, st));
+  DEV_TRY(down(g->bc_src, dg.bc_src, dg.nbc, st));
+  DEV_TRY(down(g->bc_face, dg.bc_face, dg.nbc, st));
+  DEV_TRY(hipStreamSynchronize(st));
+  g->bc_src_all.assign((size_t)dg.n, -1);
+  for (size_t k = 0; k < g->bc_cell.size(); ++k) g->bc_src_all[g->bc_cell[k]] = g->bc_src[k];
+  return 0;
+}
+
+int fetch_host_layout(const DeviceGridArrays &dg, DeviceLayout *y, hipStream_t st, std::string *err) {
+  if (!dg.xyz || !y->slot_of.empty() || dg.n == 0) return 0;
+  const int64_t nbrk = dg.nslot / 64;
+  std::vector<unsigned long long> xm;
+  DEV_TRY(down(y->slot_of, dg.slot_of, dg.n, st));
+  DEV_TRY(down(y->cell_of, dg.cell_of, dg.nslot, st));
+  DEV_TRY(down(y->nbrick, dg.nbrick, (size_t)nbrk * dg.nbp, st));
+  DEV_TRY(down(xm, dg.xmask, nbrk, st));
+  DEV_TRY(down(y->xbase, dg.xbase, nbrk, st));
+  DEV_TRY(down(y->xnbr, dg.xnbr, (size_t)dg.Qm * dg.xstride, st));
+  DEV_TRY(hipStreamSynchronize(st));
+  y->xmask.assign(xm.begin(), xm.end());
+  y->xrow_of.assign((size_t)dg.n, -1);
+  for (int64_t c = 0; c < dg.n; ++c) {
+    const int64_t s = y->slot_of[c], b = s / 64;
+    if ((y->xmask[b] >> (s & 63)) & 1ull)
+      y->xrow_of[c] = y->xbase[b] + __builtin_popcountll(y->xmask[b] & ((1ull << (s & 63)) - 1ull));
   }
-  if (dg.nbr && g->nbr.empty()) {
-    DEV_TRY(down(g->nbr, dg.nbr, (size_t)dg.Qm * dg.n, st));
-    any = true;
-  }
-  if (any) DEV_TRY(hipStreamSynchronize(st));
   return 0;
 }
 

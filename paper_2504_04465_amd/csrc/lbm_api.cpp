@@ -63,6 +63,7 @@ struct lbm_ctx {
   lbm_face_bc face[6]{};
   int dim = 0, L = 0;
   double tau[8]{};
+  int64_t rows[8]{};  // explicit rows per level
   double bpu[8]{};  // algorithmic bytes per cell update of the collide kernel, per level
   int64_t N = 0, NS = 0, Ng = 0, stride = 0;  // cells, slots, coarse ghosts, slots per population buffer
   // device
@@ -531,6 +532,15 @@ lbm_status mlp_upload_weights(lbm_ctx *c, const float *w) {
   return LBM_OK;
 }
 
+// the host copies of a device-built grid's tables, for the readers that
+// need them
+lbm_status host_tables(lbm_ctx *c) {
+  std::string err;
+  if (fetch_host_grid(c->dg, &c->g, c->stream, &err) != 0 || fetch_host_layout(c->dg, &c->lay, c->stream, &err) != 0)
+    return set_err(c, LBM_E_DEVICE, err);
+  return LBM_OK;
+}
+
 // temporaries of the device grid build, through the context's allocator
 void *build_alloc(size_t bytes, void *ctx) { return dev_alloc((lbm_ctx *)ctx, bytes); }
 void build_release(void *p, void *ctx) { dev_release((lbm_ctx *)ctx, p); }
@@ -640,7 +650,7 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
     periodic[a] = a < dim && faces[2 * a].kind == LBM_BC_PERIODIC && faces[2 * a + 1].kind == LBM_BC_PERIODIC;
   const bool on_device = c->device_build && !c->p.host_only;
   if (on_device) {
-    // the tree and its layout built on the GPU, copied into c->g / c->lay
+    // the tree and its layout built on the GPU and kept there
     auto &bi = c->bi;
     bi.dim = dim;
     bi.L = n_levels;
@@ -686,7 +696,9 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
   // after those
   c->stage.clear();
   int64_t nstage = 0;
-  if (c->p.in_place && (c->Ng > 0 || !c->g.bc_src.empty())) {
+  lbm_status s;
+  if (c->p.in_place && (c->Ng > 0 || c->g.boff[n_levels] > 0)) {
+    if ((s = host_tables(c)) != LBM_OK) return s;
     c->stage.assign((size_t)c->NS, -1);
     for (int64_t k = 0; k < c->Ng; ++k) c->stage[c->lay.slot_of[c->g.ghost_cell[k]]] = (int32_t)(c->NS + k);
     for (size_t k = 0; k < c->g.bc_src.size(); ++k) {
@@ -704,11 +716,12 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
     for (int l = 0; l < n_levels; ++l) {
       const int64_t ncell = c->g.off[l + 1] - c->g.off[l];
       const int64_t nsl = c->lay.soff[l + 1] - c->lay.soff[l];
-      int64_t nx = 0, nsp = 0;
-      for (int64_t k = c->g.off[l]; k < c->g.off[l + 1]; ++k) {
+      int64_t nx = on_device ? c->dg.rows[l] : 0, nsp = on_device ? c->dg.sponge[l] : 0;
+      for (int64_t k = c->g.off[l]; !on_device && k < c->g.off[l + 1]; ++k) {
         nx += c->lay.xrow_of[k] >= 0;
         nsp += (c->g.flag[k] & F_SPONGE) != 0;
       }
+      c->rows[l] = nx;
       const double tables = nsl * (1.0 + (c->lay.nbp * 4.0 + 12.0) / 64.0) + nx * 4.0 * (Q - 1) + nsp * 16.0;
       c->bpu[l] = ncell > 0 ? pops + tables / (double)ncell : pops;
     }
@@ -737,20 +750,26 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
       if (!c->gb[b]) return set_err(c, LBM_E_NOMEM, "population allocation failed");
     }
   }
-  lbm_status s;
-  if ((s = upload(c, &c->d_nbrick, y.nbrick.data(), y.nbrick.size())) != LBM_OK) return s;
-  if ((s = upload(c, &c->d_xmask, y.xmask.data(), y.xmask.size())) != LBM_OK) return s;
-  if ((s = upload(c, &c->d_xbase, y.xbase.data(), y.xbase.size())) != LBM_OK) return s;
-  if ((s = upload(c, &c->d_xnbr, y.xnbr.data(), y.xnbr.size())) != LBM_OK) return s;
-  {
-    std::vector<uint64_t> xreg;
-    regular_pulls(y, c->lat, &xreg);
-    if ((s = upload(c, &c->d_xreg, xreg.data(), xreg.size())) != LBM_OK) return s;
-  }
-  if ((s = upload(c, &c->d_cell_of, y.cell_of.data(), y.cell_of.size())) != LBM_OK) return s;
-  if (c->dg.slot_of) c->d_slot_of = c->dg.slot_of;
-  else if ((s = upload(c, &c->d_slot_of, y.slot_of.data(), y.slot_of.size())) != LBM_OK) return s;
-  if (c->dg.nbr) {
+  if (on_device) {
+    // the builder left the tables and the lists over slots on the device
+    const DeviceGridArrays &k = c->dg;
+    c->d_nbrick = k.nbrick;
+    c->d_xmask = (uint64_t *)k.xmask;
+    c->d_xbase = k.xbase;
+    c->d_xnbr = k.xnbr;
+    c->d_xreg = k.xreg;
+    c->d_cell_of = k.cell_of;
+    c->d_slot_of = k.slot_of;
+    c->d_sigma = k.sigma;
+    c->d_rhoinf = k.rho_inf;
+    c->d_ghost = k.ghost_slot;
+    c->d_child = k.child_slot;
+    c->d_crow = k.child_row;
+    c->d_xghost = k.row_ghost;
+    c->d_unknown = k.unknown;
+    c->d_bc_cell = k.bc_cell_slot;
+    c->d_bc_src = k.bc_src_slot;
+    c->d_bc_face = k.bc_face;
     c->d_flags = (uint8_t *)dev_alloc(c, std::max<int64_t>(NS, 1));
     if (!c->d_flags) return set_err(c, LBM_E_NOMEM, "flag allocation failed");
     launch_slot_flags(c->dg, NS, c->d_flags, c->stream);
@@ -758,69 +777,82 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
     dev_release(c, c->dg.nbr);  // (Q-1) x 4 B per cell the update never reads
     c->dg.nbr = nullptr;
   } else {
-    // device flags per slot: the canonical ones, F_MOVING where a population
-    // is pulled from a moving wall, F_HOLE for slots without a cell
-    std::vector<uint8_t> fl(NS, (uint8_t)F_HOLE);
-#pragma omp parallel for schedule(static)
-    for (int64_t cc = 0; cc < N; ++cc) {
-      uint8_t v = c->g.flag[cc];
-      for (int i = 0; i < Qm; ++i)
-        if (c->g.nbr[(size_t)i * N + cc] <= -3) v |= F_MOVING;
-      fl[y.slot_of[cc]] = v;
+    if ((s = upload(c, &c->d_nbrick, y.nbrick.data(), y.nbrick.size())) != LBM_OK) return s;
+    if ((s = upload(c, &c->d_xmask, y.xmask.data(), y.xmask.size())) != LBM_OK) return s;
+    if ((s = upload(c, &c->d_xbase, y.xbase.data(), y.xbase.size())) != LBM_OK) return s;
+    if ((s = upload(c, &c->d_xnbr, y.xnbr.data(), y.xnbr.size())) != LBM_OK) return s;
+    {
+      std::vector<uint64_t> xreg;
+      regular_pulls(y, c->lat, &xreg);
+      if ((s = upload(c, &c->d_xreg, xreg.data(), xreg.size())) != LBM_OK) return s;
     }
-    if ((s = upload(c, &c->d_flags, fl.data(), fl.size())) != LBM_OK) return s;
-  }
-  if (!c->g.sigma.empty()) {
-    std::vector<double> sg(NS, 0.0), ri(NS, 0.0);
-    for (int64_t cc = 0; cc < N; ++cc) {
-      sg[y.slot_of[cc]] = c->g.sigma[cc];
-      ri[y.slot_of[cc]] = c->g.rho_inf[cc];
+    if ((s = upload(c, &c->d_cell_of, y.cell_of.data(), y.cell_of.size())) != LBM_OK) return s;
+    if ((s = upload(c, &c->d_slot_of, y.slot_of.data(), y.slot_of.size())) != LBM_OK) return s;
+    {
+      // device flags per slot: the canonical ones, F_MOVING where a population
+      // is pulled from a moving wall, F_HOLE for slots without a cell
+      std::vector<uint8_t> fl(NS, (uint8_t)F_HOLE);
+  #pragma omp parallel for schedule(static)
+      for (int64_t cc = 0; cc < N; ++cc) {
+        uint8_t v = c->g.flag[cc];
+        for (int i = 0; i < Qm; ++i)
+          if (c->g.nbr[(size_t)i * N + cc] <= -3) v |= F_MOVING;
+        fl[y.slot_of[cc]] = v;
+      }
+      if ((s = upload(c, &c->d_flags, fl.data(), fl.size())) != LBM_OK) return s;
     }
-    if ((s = upload(c, &c->d_sigma, sg.data(), sg.size())) != LBM_OK) return s;
-    if ((s = upload(c, &c->d_rhoinf, ri.data(), ri.size())) != LBM_OK) return s;
+    if (!c->g.sigma.empty()) {
+      std::vector<double> sg(NS, 0.0), ri(NS, 0.0);
+      for (int64_t cc = 0; cc < N; ++cc) {
+        sg[y.slot_of[cc]] = c->g.sigma[cc];
+        ri[y.slot_of[cc]] = c->g.rho_inf[cc];
+      }
+      if ((s = upload(c, &c->d_sigma, sg.data(), sg.size())) != LBM_OK) return s;
+      if ((s = upload(c, &c->d_rhoinf, ri.data(), ri.size())) != LBM_OK) return s;
+    }
+    {
+      // ghost, child and boundary lists over slots; every child of a coarse
+      // ghost has an exception row, which the coalescence pulls through
+      std::vector<int32_t> gs(c->g.ghost_cell.size()), ch(c->g.child.size()), cr(c->g.child.size(), 0);
+      for (size_t k = 0; k < gs.size(); ++k) gs[k] = y.slot_of[c->g.ghost_cell[k]];
+      for (size_t k = 0; k < ch.size(); ++k) {
+        const int32_t v = c->g.child[k];
+        ch[k] = v < 0 ? -1 : y.slot_of[v];
+        if (v >= 0) {
+          cr[k] = y.xrow_of[v];
+          if (cr[k] < 0) return set_err(c, LBM_E_ARG, "internal: child of a coarse ghost without an exception row");
+        }
+      }
+      std::vector<int32_t> bcc(c->g.bc_cell.size()), bcs(c->g.bc_src.size());
+      for (size_t k = 0; k < bcc.size(); ++k) bcc[k] = y.slot_of[c->g.bc_cell[k]];
+      for (size_t k = 0; k < bcs.size(); ++k) bcs[k] = y.slot_of[c->g.bc_src[k]];
+      // a coarse ghost pulls at least one population from its children, so it
+      // has an explicit row, which names its entry in the child table
+      std::vector<int32_t> xg((size_t)std::max<int64_t>(y.nx, 1), -1);
+      for (size_t k = 0; k < gs.size(); ++k) {
+        const int32_t r = y.xrow_of[c->g.ghost_cell[k]];
+        if (r < 0) return set_err(c, LBM_E_ARG, "internal: coarse ghost without an exception row");
+        xg[r] = (int32_t)k;
+      }
+      if ((s = upload(c, &c->d_xghost, xg.data(), xg.size())) != LBM_OK) return s;
+      // the collide explodes before the boundary fills read their sources: no
+      // source is a fine ghost, whose parent would be a coarse ghost at depth
+      // B / 2 < B from the face, inside the coarse boundary layer
+      for (int32_t src : c->g.bc_src)
+        if (c->g.flag[src] & F_FINE_GHOST) return set_err(c, LBM_E_ARG, "internal: boundary source is a fine ghost");
+      if ((s = upload(c, &c->d_ghost, gs.data(), gs.size())) != LBM_OK) return s;
+      if ((s = upload(c, &c->d_child, ch.data(), ch.size())) != LBM_OK) return s;
+      if ((s = upload(c, &c->d_crow, cr.data(), cr.size())) != LBM_OK) return s;
+      if ((s = upload(c, &c->d_bc_cell, bcc.data(), bcc.size())) != LBM_OK) return s;
+      if ((s = upload(c, &c->d_bc_src, bcs.data(), bcs.size())) != LBM_OK) return s;
+    }
+    if ((s = upload(c, &c->d_unknown, c->g.unknown.data(), c->Ng)) != LBM_OK) return s;
+    if ((s = upload(c, &c->d_bc_face, c->g.bc_face.data(), c->g.bc_face.size())) != LBM_OK) return s;
   }
   if (c->lamf) {
     c->d_lam = dev_alloc(c, (size_t)c->lam_bytes * NLAM * c->stride);
     if (!c->d_lam) return set_err(c, LBM_E_NOMEM, "multiplier allocation failed");
   }
-  {
-    // ghost, child and boundary lists over slots; every child of a coarse
-    // ghost has an exception row, which the coalescence pulls through
-    std::vector<int32_t> gs(c->g.ghost_cell.size()), ch(c->g.child.size()), cr(c->g.child.size(), 0);
-    for (size_t k = 0; k < gs.size(); ++k) gs[k] = y.slot_of[c->g.ghost_cell[k]];
-    for (size_t k = 0; k < ch.size(); ++k) {
-      const int32_t v = c->g.child[k];
-      ch[k] = v < 0 ? -1 : y.slot_of[v];
-      if (v >= 0) {
-        cr[k] = y.xrow_of[v];
-        if (cr[k] < 0) return set_err(c, LBM_E_ARG, "internal: child of a coarse ghost without an exception row");
-      }
-    }
-    std::vector<int32_t> bcc(c->g.bc_cell.size()), bcs(c->g.bc_src.size());
-    for (size_t k = 0; k < bcc.size(); ++k) bcc[k] = y.slot_of[c->g.bc_cell[k]];
-    for (size_t k = 0; k < bcs.size(); ++k) bcs[k] = y.slot_of[c->g.bc_src[k]];
-    // a coarse ghost pulls at least one population from its children, so it
-    // has an explicit row, which names its entry in the child table
-    std::vector<int32_t> xg((size_t)std::max<int64_t>(y.nx, 1), -1);
-    for (size_t k = 0; k < gs.size(); ++k) {
-      const int32_t r = y.xrow_of[c->g.ghost_cell[k]];
-      if (r < 0) return set_err(c, LBM_E_ARG, "internal: coarse ghost without an exception row");
-      xg[r] = (int32_t)k;
-    }
-    if ((s = upload(c, &c->d_xghost, xg.data(), xg.size())) != LBM_OK) return s;
-    // the collide explodes before the boundary fills read their sources: no
-    // source is a fine ghost, whose parent would be a coarse ghost at depth
-    // B / 2 < B from the face, inside the coarse boundary layer
-    for (int32_t src : c->g.bc_src)
-      if (c->g.flag[src] & F_FINE_GHOST) return set_err(c, LBM_E_ARG, "internal: boundary source is a fine ghost");
-    if ((s = upload(c, &c->d_ghost, gs.data(), gs.size())) != LBM_OK) return s;
-    if ((s = upload(c, &c->d_child, ch.data(), ch.size())) != LBM_OK) return s;
-    if ((s = upload(c, &c->d_crow, cr.data(), cr.size())) != LBM_OK) return s;
-    if ((s = upload(c, &c->d_bc_cell, bcc.data(), bcc.size())) != LBM_OK) return s;
-    if ((s = upload(c, &c->d_bc_src, bcs.data(), bcs.size())) != LBM_OK) return s;
-  }
-  if ((s = upload(c, &c->d_unknown, c->g.unknown.data(), c->Ng)) != LBM_OK) return s;
-  if ((s = upload(c, &c->d_bc_face, c->g.bc_face.data(), c->g.bc_face.size())) != LBM_OK) return s;
   if (!c->stage.empty()) {
     // where coarse ghosts and boundary-layer sources leave their
     // post-collision populations when streaming in place
@@ -860,6 +892,8 @@ lbm_status lbm_layout_export(lbm_ctx *c, int32_t *slot_of, int32_t *xrow_of, int
                              int32_t *xnbr) {
   if (!c) return LBM_E_ARG;
   if (!c->have_grid) return set_err(c, LBM_E_STATE, "no grid");
+  const lbm_status s = host_tables(c);
+  if (s != LBM_OK) return s;
   const DeviceLayout &y = c->lay;
   const int64_t n = c->g.n, nb = y.nslot / 64, Qm = c->lat.Q - 1;
   if (slot_of) std::copy(y.slot_of.begin(), y.slot_of.end(), slot_of);
@@ -881,11 +915,7 @@ lbm_status lbm_layout_info(lbm_ctx *c, int64_t *n_slots, int64_t *n_rows, int64_
   if (n_rows) *n_rows = c->lay.nx;
   for (int l = 0; l < c->L; ++l) {
     if (slots_per_level) slots_per_level[l] = c->lay.soff[l + 1] - c->lay.soff[l];
-    if (rows_per_level) {
-      int64_t k = 0;
-      for (int64_t q = c->g.off[l]; q < c->g.off[l + 1]; ++q) k += c->lay.xrow_of[q] >= 0;
-      rows_per_level[l] = k;
-    }
+    if (rows_per_level) rows_per_level[l] = c->rows[l];
   }
   return LBM_OK;
 }
@@ -896,11 +926,11 @@ lbm_status lbm_grid_export(lbm_ctx *c, int32_t *coords, int8_t *level, uint8_t *
   if (!c->have_grid) return set_err(c, LBM_E_STATE, "no grid");
   const int64_t n = c->N;
   const int Qm = c->lat.Q - 1;
-  if (coords || nbr) {
-    // a device-built grid keeps its coordinates on the device, and not its
+  {
+    // a device-built grid keeps its tables on the device, and not its
     // canonical neighbour list: that comes from building the grid again
     std::string err;
-    if (fetch_host_mirror(c->dg, &c->g, c->stream, &err) != 0) return set_err(c, LBM_E_DEVICE, err);
+    if (fetch_host_grid(c->dg, &c->g, c->stream, &err) != 0) return set_err(c, LBM_E_DEVICE, err);
     if (nbr && c->g.nbr.empty()) {
       const auto &bi = c->bi;
       HostGrid tg;
@@ -1051,6 +1081,14 @@ lbm_status lbm_remesh(lbm_ctx *c, const lbm_mask *refine, const lbm_mask *solid)
     release_old();
     return s;
   }
+  if (!c->device_build) {
+    // the host list builder reads the old tree's tables
+    std::string err;
+    if (fetch_host_grid(c->dg, &c->g, c->stream, &err) != 0) {
+      release_old();
+      return set_err(c, LBM_E_DEVICE, err);
+    }
+  }
   // 2. the new tree: same extent, levels and faces.  The old tree's device
   // tables (a device-built grid) are taken out of the context's allocations
   // so that the new build leaves them for the source lists.
@@ -1112,8 +1150,7 @@ lbm_status lbm_remesh(lbm_ctx *c, const lbm_mask *refine, const lbm_mask *solid)
     std::vector<int32_t> src;
     std::vector<double> wt;
     // host lists need both trees' coordinates on the host
-    if (fetch_host_mirror(old_dg, &prev, c->stream, &err) != 0 ||
-        fetch_host_mirror(c->dg, &c->g, c->stream, &err) != 0) {
+    if (fetch_host_grid(c->dg, &c->g, c->stream, &err) != 0) {
       release_all();
       return set_err(c, LBM_E_DEVICE, err);
     }
@@ -1329,6 +1366,7 @@ lbm_status lbm_set_inflow_noise(lbm_ctx *c, const double *du) {
   // cell's explicit row (a cell with a moving-wall link always has one)
   const int64_t xs = c->lay.xstride, n = c->N;
   const int Q = c->lat.Q;
+  if (const lbm_status s = host_tables(c); s != LBM_OK) return s;
   std::vector<double> h((size_t)(Q - 1) * xs, 0.0);
   for (int64_t k = 0; k < n; ++k) {
     const int64_t r = c->lay.xrow_of[k];
@@ -1430,7 +1468,8 @@ lbm_status lbm_get_cells(lbm_ctx *c, const int64_t *cells, int64_t n, double *f,
   std::vector<int> lev(n);
   for (int64_t k = 0; k < n; ++k) {
     if (cells[k] < 0 || cells[k] >= c->N) return set_err(c, LBM_E_ARG, "cell index out of range");
-    lev[k] = c->g.lev[cells[k]];
+    // the cells of a level are contiguous
+    lev[k] = (int)(std::upper_bound(c->g.off + 1, c->g.off + c->L, cells[k]) - (c->g.off + 1));
     lbeg[lev[k] + 1]++;
   }
   for (int l = 0; l < c->L; ++l) lbeg[l + 1] += lbeg[l];
