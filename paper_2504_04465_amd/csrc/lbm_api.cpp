@@ -1665,7 +1665,7 @@ lbm_status lbm_mlp_grad(lbm_ctx *c, const float *xh, const float *th, int64_t n,
   HIP_TRY(c, hipMemcpyAsync(dp, perm.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipMemsetAsync(c->d_mlp_g, 0, sizeof(float) * MLP_PARAMS, c->stream));
   HIP_TRY(c, hipMemsetAsync(c->d_mlp_loss, 0, sizeof(float), c->stream));
-  mlp_train_batch(c->d_mlp_ops, dx, dt, dp, 0, n, gp, c->d_mlp_g, c->d_mlp_loss, c->stream);
+  mlp_grad_batch(c->d_mlp_ops, dx, dt, dp, n, gp, c->d_mlp_g, c->d_mlp_loss, c->stream);
   lbm_status s = check_launch(c);
   if (s != LBM_OK) return s;
   float lh = 0.0f;
@@ -1684,64 +1684,33 @@ lbm_status lbm_mlp_train(lbm_ctx *c, const double *x, const double *lambda, int6
   lbm_status s = mlp_ensure(c);
   if (s != LBM_OK) return s;
   std::mt19937_64 rng(seed);
-  std::vector<float> w(MLP_PARAMS, 0.0f);
-  if (c->have_mlp) {
-    HIP_TRY(c, hipMemcpy(w.data(), c->d_mlp_w, sizeof(float) * MLP_PARAMS, hipMemcpyDeviceToHost));
-  } else {
+  if (!c->have_mlp) {
     // uniform initialisation scaled by the fan-in; biases zero
+    std::vector<float> w(MLP_PARAMS, 0.0f);
     const int offs[4] = {0, 320, 4480, 8640}, fan[4] = {4, 64, 64, 64}, cnt[4] = {256, 4096, 4096, 512};
     for (int k = 0; k < 4; ++k) {
       std::uniform_real_distribution<double> U(-1.0, 1.0);
       const double lim = 0.5 * std::sqrt(6.0 / fan[k]);
       for (int q = 0; q < cnt[k]; ++q) w[offs[k] + q] = (float)(lim * U(rng));
     }
+    HIP_TRY(c, hipMemcpy(c->d_mlp_w, w.data(), sizeof(float) * MLP_PARAMS, hipMemcpyHostToDevice));
   }
-  // the network learns the canonical octant u_x >= u_y >= 0 (reflection
-  // symmetry of the lattice); map every sample and its label there
-  std::vector<double> xc(x, x + 4 * n), lc(lambda, lambda + 8 * n);
-  for (int64_t i = 0; i < n; ++i) {
-    double *xi = &xc[4 * i], *li = &lc[8 * i];
-    if (xi[1] < 0.0) { xi[1] = -xi[1]; li[1] = -li[1]; li[4] = -li[4]; li[6] = -li[6]; }
-    if (xi[2] < 0.0) { xi[2] = -xi[2]; li[2] = -li[2]; li[4] = -li[4]; li[7] = -li[7]; }
-    if (xi[2] > xi[1]) {
-      std::swap(xi[1], xi[2]);
-      std::swap(li[1], li[2]);
-      std::swap(li[3], li[5]);
-      std::swap(li[6], li[7]);
-    }
-  }
-  x = xc.data();
-  lambda = lc.data();
-  // output normalisation from the labels
-  double mu[8] = {0}, sg[8] = {0};
-  for (int64_t i = 0; i < n; ++i)
-    for (int k = 0; k < 8; ++k) mu[k] += lambda[i * 8 + k];
-  for (int k = 0; k < 8; ++k) mu[k] /= (double)n;
-  for (int64_t i = 0; i < n; ++i)
-    for (int k = 0; k < 8; ++k) sg[k] += (lambda[i * 8 + k] - mu[k]) * (lambda[i * 8 + k] - mu[k]);
-  for (int k = 0; k < 8; ++k) {
-    sg[k] = std::sqrt(sg[k] / (double)n);
-    if (!(sg[k] > 1e-12)) sg[k] = 1.0;
-    w[9160 + k] = (float)mu[k];
-    w[9168 + k] = (float)sg[k];
-  }
-  if ((s = mlp_upload_weights(c, w.data())) != LBM_OK) return s;
-  std::vector<float> xh(4 * n), th(8 * n);
-  for (int64_t i = 0; i < n; ++i) {
-    xh[4 * i] = (float)((x[4 * i] - 2.6) / 2.4);
-    xh[4 * i + 1] = (float)(x[4 * i + 1] / 2.5);
-    xh[4 * i + 2] = (float)(x[4 * i + 2] / 2.5);
-    xh[4 * i + 3] = (float)((x[4 * i + 3] - 1.75) / 1.25);
-    for (int k = 0; k < 8; ++k) th[8 * i + k] = (float)((lambda[8 * i + k] - mu[k]) / sg[k]);
-  }
+  // canonical octant, output normalisation from the labels, normalised
+  // samples: on the device, while the host shuffles the first epoch
   CallBuffers tmp(c);
+  double *rx = (double *)tmp.take(sizeof(double) * 4 * n);
+  double *rl = (double *)tmp.take(sizeof(double) * 8 * n);
+  double *st = (double *)tmp.take(mlp_prepare_bytes(n));
   float *dx = (float *)tmp.take(sizeof(float) * 4 * n);
   float *dt = (float *)tmp.take(sizeof(float) * 8 * n);
   int32_t *dp = (int32_t *)tmp.take(sizeof(int32_t) * n);
   float *gp = (float *)tmp.take(mlp_partials_bytes(batch));
-  if (!dx || !dt || !dp || !gp) return set_err(c, LBM_E_NOMEM, "training allocation failed");
-  HIP_TRY(c, hipMemcpyAsync(dx, xh.data(), sizeof(float) * 4 * n, hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(dt, th.data(), sizeof(float) * 8 * n, hipMemcpyHostToDevice, c->stream));
+  if (!rx || !rl || !st || !dx || !dt || !dp || !gp) return set_err(c, LBM_E_NOMEM, "training allocation failed");
+  HIP_TRY(c, hipMemcpyAsync(rx, x, sizeof(double) * 4 * n, hipMemcpyHostToDevice, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(rl, lambda, sizeof(double) * 8 * n, hipMemcpyHostToDevice, c->stream));
+  mlp_prepare(rx, rl, n, st + 16, st, c->d_mlp_w, dx, dt, c->stream);
+  mlp_operands(c->d_mlp_w, c->d_mlp_ops, c->stream);
+  c->have_mlp = true;
   HIP_TRY(c, hipMemsetAsync(c->d_mlp_m, 0, sizeof(float) * MLP_PARAMS, c->stream));
   HIP_TRY(c, hipMemsetAsync(c->d_mlp_v, 0, sizeof(float) * MLP_PARAMS, c->stream));
   HIP_TRY(c, hipMemsetAsync(c->d_mlp_g, 0, sizeof(float) * MLP_PARAMS, c->stream));
@@ -1761,8 +1730,8 @@ lbm_status lbm_mlp_train(lbm_ctx *c, const double *x, const double *lambda, int6
       ++t;
       const double frac = (double)(t - 1) / (double)std::max<int64_t>(total, 1);
       const float lr_t = (float)(lr * (0.01 + 0.99 * 0.5 * (1.0 + std::cos(3.14159265358979323846 * frac))));
-      mlp_train_batch(c->d_mlp_ops, dx, dt, dp, b * batch, batch, gp, c->d_mlp_g, c->d_mlp_loss, c->stream);
-      mlp_adam(c->d_mlp_w, c->d_mlp_m, c->d_mlp_v, c->d_mlp_g, c->d_mlp_ops, lr_t, t, c->stream);
+      mlp_train_batch(c->d_mlp_ops, dx, dt, dp, b * batch, batch, gp, c->d_mlp_loss, c->d_mlp_w, c->d_mlp_m,
+                      c->d_mlp_v, lr_t, t, c->stream);
     }
     if ((s = check_launch(c)) != LBM_OK) return s;
     float lh = 0.0f;

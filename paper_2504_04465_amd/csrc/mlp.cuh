@@ -74,20 +74,28 @@ __device__ inline float dsilu_f(float z) {
   return s * (1.0f + z * (1.0f - s));
 }
 
-// acc(32 x 32) = A[32 x K] (LDS row-major, lda) * B, with B[k][n] = W[n0 + n][k]
-// (W row-major in global memory, ldw)
+// B operands of a 32-column tile, B[k][n] = W[n0 + n][k] (W row-major in
+// global memory, ldw)
 template <int K>
-__device__ inline f32x16 gemm_aw(const __bf16 *A, int lda, const __bf16 *W, int ldw, int n0) {
+struct WTile {
+  bf16x8 b[K / 16];
+  __device__ inline void load(const __bf16 *W, int ldw, int n0) {
+    const int l = threadIdx.x & 63;
+#pragma unroll
+    for (int q = 0; q < K / 16; ++q) b[q] = *(const bf16x8 *)(W + (n0 + (l & 31)) * ldw + 16 * q + 8 * (l >> 5));
+  }
+};
+
+// acc(32 x 32) = A[32 x K] (LDS row-major, lda) * B
+template <int K>
+__device__ inline f32x16 gemm_aw(const __bf16 *A, int lda, const WTile<K> &w) {
   const int l = threadIdx.x & 63;
   f32x16 acc;
 #pragma unroll
   for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    const bf16x8 a = *(const bf16x8 *)(A + (l & 31) * lda + k0 + 8 * (l >> 5));
-    const bf16x8 b = *(const bf16x8 *)(W + (n0 + (l & 31)) * ldw + k0 + 8 * (l >> 5));
-    acc = mfma32(a, b, acc);
-  }
+  for (int q = 0; q < K / 16; ++q)
+    acc = mfma32(*(const bf16x8 *)(A + (l & 31) * lda + 16 * q + 8 * (l >> 5)), w.b[q], acc);
   return acc;
 }
 
@@ -141,66 +149,55 @@ __device__ inline void mlp_input_row(__bf16 *xin_row, float rho, float ux, float
   for (int k = 8; k < 16; ++k) xin_row[k] = (__bf16)0.0f;
 }
 
-// Between the layers only the wavefront that owns a tile reads what its
-// lanes wrote to LDS (every caller gives each wavefront its own tile), so
-// waiting for the wavefront's own LDS writes suffices; a block barrier
-// would make the block's wavefronts wait for each other.
-__device__ inline void lds_wave_sync() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
-// forward of one 32-sample tile held by one wavefront.  xin [32][16],
-// ha / hb [32][64] scratch, y [32][8] output (normalised), z (optional,
-// training) [3][32][64] pre-activations, h (optional) keeps h1..h3 in
-// ha, hb, hc for the backward pass.
-__device__ inline void mlp_forward_tile(const MlpOperands *P, const __bf16 *xin, __bf16 *h1,
-                                        __bf16 *h2, __bf16 *h3, float *y, float *z) {
-  const int l = threadIdx.x & 63;
-#pragma unroll
-  for (int n0 = 0; n0 < 64; n0 += 32) {
-    const f32x16 acc = gemm_aw<16>(xin, 16, P->w1, 16, n0);
+// Forward of one 32-sample tile held by one block of at least two
+// wavefronts, in training: wavefronts 0 and 1 take the two 32-column tiles of
+// each hidden layer; every thread of the block calls it.  xin [32][16];
+// h1..h3 [32][64] activations, z [3][32][64] pre-activations and y [32][8]
+// (normalised) outputs in LDS.  The weights of all layers are read before the
+// first, so that their latency is paid once.
+__device__ inline void mlp_forward_tile(const MlpOperands *P, const __bf16 *xin, __bf16 *h1, __bf16 *h2, __bf16 *h3,
+                                        float *y, float *z, int wv) {
+  const int l = threadIdx.x & 63, n0 = 32 * (wv & 1);
+  const bool chain = wv < 2;
+  const int col = n0 + (l & 31);
+  WTile<16> w1;
+  WTile<64> w2, w3, w4;
+  float b1 = 0.0f, b2 = 0.0f, b3 = 0.0f, b4 = 0.0f;
+  if (chain) {
+    w1.load(P->w1, 16, n0);
+    w2.load(P->w2, 64, n0);
+    w3.load(P->w3, 64, n0);
+    w4.load(P->w4, 64, 0);
+    b1 = P->b1[col];
+    b2 = P->b2[col];
+    b3 = P->b3[col];
+    b4 = P->b4[l & 31];
+  }
+  auto hidden = [&](const f32x16 &acc, float bias, float *zl, __bf16 *h) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int row = c_row(l, r), col = n0 + (l & 31);
-      const float v = acc[r] + P->b1[col];
-      if (z) z[row * 64 + col] = v;
-      h1[row * 64 + col] = (__bf16)silu_f(v);
+      const int row = c_row(l, r);
+      const float v = acc[r] + bias;
+      zl[row * 64 + col] = v;
+      h[row * 64 + col] = (__bf16)silu_f(v);
     }
-  }
-  lds_wave_sync();
-#pragma unroll
-  for (int n0 = 0; n0 < 64; n0 += 32) {
-    const f32x16 acc = gemm_aw<64>(h1, 64, P->w2, 64, n0);
+  };
+  if (chain) hidden(gemm_aw<16>(xin, 16, w1), b1, z, h1);
+  __syncthreads();
+  if (chain) hidden(gemm_aw<64>(h1, 64, w2), b2, z + 2048, h2);
+  __syncthreads();
+  if (chain) hidden(gemm_aw<64>(h2, 64, w3), b3, z + 4096, h3);
+  __syncthreads();
+  if (wv == 0) {
+    const f32x16 acc = gemm_aw<64>(h3, 64, w4);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int row = c_row(l, r), col = n0 + (l & 31);
-      const float v = acc[r] + P->b2[col];
-      if (z) z[2048 + row * 64 + col] = v;
-      h2[row * 64 + col] = (__bf16)silu_f(v);
+      const int row = c_row(l, r), c = l & 31;
+      if (c < 8) y[row * 8 + c] = acc[r] + b4;
     }
   }
-  lds_wave_sync();
-#pragma unroll
-  for (int n0 = 0; n0 < 64; n0 += 32) {
-    const f32x16 acc = gemm_aw<64>(h2, 64, P->w3, 64, n0);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = c_row(l, r), col = n0 + (l & 31);
-      const float v = acc[r] + P->b3[col];
-      if (z) z[4096 + row * 64 + col] = v;
-      h3[row * 64 + col] = (__bf16)silu_f(v);
-    }
-  }
-  lds_wave_sync();
-  {
-    const f32x16 acc = gemm_aw<64>(h3, 64, P->w4, 64, 0);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int row = c_row(l, r), col = l & 31;
-      if (col < 8) y[row * 8 + col] = acc[r] + P->b4[col];
-    }
-  }
-  lds_wave_sync();
+  __syncthreads();
 }
-
 
 // ---------------------------------------------------------------------------
 // inference of a whole wavefront's 64 samples (two tiles of 32), weights in
