@@ -32,7 +32,7 @@ constexpr int BLOCK = 256;
 
 // ---------------------------------------------------------------------------
 // storage traits: FP64, FP32, FP16 holding f_i - w_i (compute in FP32).
-// stn is a streaming (non-temporal) store: the collide kernel's output is not
+// stn (stg, on a global pointer; sta is its plain form) is a streaming (non-temporal) store: the collide kernel's output is not
 // read again before the level's next update, so it should not displace the
 // neighbour lines that other wavefronts still pull from the L2.
 // ---------------------------------------------------------------------------
@@ -61,6 +61,7 @@ struct Sto<double> {
   __device__ static void stn(double *p, int64_t k, C v, double) { __builtin_nontemporal_store(v, p + k); }
   __device__ static void stp(double *p, C v, double) { __builtin_nontemporal_store(v, p); }
   __device__ static void stg(gptr<double> p, C v, double) { __builtin_nontemporal_store(v, p); }
+  __device__ static void sta(gptr<double> p, C v, double) { *p = v; }
 };
 template <>
 struct Sto<float> {
@@ -72,6 +73,7 @@ struct Sto<float> {
   __device__ static void stn(float *p, int64_t k, C v, double) { __builtin_nontemporal_store(v, p + k); }
   __device__ static void stp(float *p, C v, double) { __builtin_nontemporal_store(v, p); }
   __device__ static void stg(gptr<float> p, C v, double) { __builtin_nontemporal_store(v, p); }
+  __device__ static void sta(gptr<float> p, C v, double) { *p = v; }
 };
 template <>
 struct Sto<__half> {
@@ -101,6 +103,7 @@ struct Sto<__half> {
   __device__ static void stg(gptr<__half> p, C v, double w) {
     __builtin_nontemporal_store(__half_as_ushort(cvt(v, w)), (gptr<unsigned short>)p);
   }
+  __device__ static void sta(gptr<__half> p, C v, double w) { *(gptr<unsigned short>)p = __half_as_ushort(cvt(v, w)); }
 };
 
 // Newton multipliers (warm start of the numerical equilibrium) are kept in
@@ -336,7 +339,12 @@ __device__ inline void gather(const S *fin, const S *gin, const Topo &tp, const 
 // wall, back to the cell's own row opp(i) with the moving-wall correction of
 // population opp(i) (the bounce-back the next pull would have applied).
 // RAW: f holds f_i - w_i (FP16 storage), stored as it is.
-template <class L, class S, bool DDF, bool RAW = false>
+// A pushed line is written in parts by up to eight wavefronts, so these stores
+// go through the L2 (sta), which merges the parts that meet there; streaming
+// stores (as the pull's whole lines take) made the odd step of a 160 x 80 x 80
+// sphere 59.1 us a launch instead of 55.4.  With 32-bit offsets (O32, buffers
+// under 4 GB) it is 52.2; the even step, which writes whole lines, 26.7.
+template <class L, class S, bool DDF, bool RAW = false, bool O32 = false>
 __device__ inline void push_store(S *fout, S *gout, const Topo &tp, const uint32_t *nbs, int64_t c,
                                   int lane, int32_t brick, uint64_t xm, const double (&uw)[6][3], double cs2w,
                                   const typename Sto<S>::C *f, const typename Sto<S>::C *g) {
@@ -368,20 +376,21 @@ __device__ inline void push_store(S *fout, S *gout, const Topo &tp, const uint32
     char *fb = (char *)fout;
     char *gb = (char *)gout;
     constexpr int64_t rbytes = PCH * (int64_t)sizeof(S);
+    using OffT = std::conditional_t<O32, uint32_t, uint64_t>;
     {
 #pragma unroll
       for (int i = 1; i < L::Q; ++i) {
         // x + xi_i is the pull source of the opposite population
         const int j = L::S.opp[i];
         const uint32_t k = K[0][cx_<L>(j, 0) + R] + K[1][cx_<L>(j, 1) + R] + K[2][cx_<L>(j, 2) + R];
-        const uint64_t off = (uint64_t)nbs[k >> 18] * (64u * sizeof(S)) + (k & 0xffffu);
+        const OffT off = (OffT)nbs[k >> 18] * (OffT)(64u * sizeof(S)) + (OffT)(k & 0xffffu);
         auto row = (gptr<char>)(fb + i * rbytes);
         asm("" : "+s"(row));  // uniform row base in SGPRs
-        Sto<S>::stg((gptr<S>)(row + off), f[i], RAW ? 0.0 : L::S.w[i]);
+        Sto<S>::sta((gptr<S>)(row + off), f[i], RAW ? 0.0 : L::S.w[i]);
         if (DDF) {
           auto grow = (gptr<char>)(gb + i * rbytes);
           asm("" : "+s"(grow));
-          Sto<S>::stg((gptr<S>)(grow + off), g[i], 0.0);
+          Sto<S>::sta((gptr<S>)(grow + off), g[i], 0.0);
         }
       }
     }
@@ -1284,7 +1293,7 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
     }
   }
   if constexpr (AA == 2) {
-    push_store<L, S, DDF, SH>(fout, gout, a.topo, nbs[0], c, threadIdx.x & 63, brick,
+    push_store<L, S, DDF, SH, O32>(fout, gout, a.topo, nbs[0], c, threadIdx.x & 63, brick,
                           xm, a.ph.uw, a.ph.cs2w, f, g);
   } else {
     // row base (uniform: a wavefront's brick lies in one chunk) + the
@@ -1846,6 +1855,7 @@ struct Launch {
     constexpr int CB = CollideBlock<L, COLL>::value;
     const unsigned nb = (unsigned)((a.count + CB - 1) / CB);
     if (a.aa == 1) hipLaunchKernelGGL((k_collide<L, COLL, S, false, 1>), dim3(nb), dim3(CB), 0, s, a);
+    else if (a.aa == 2 && a.topo.off32) hipLaunchKernelGGL((k_collide<L, COLL, S, false, 2, false, true>), dim3(nb), dim3(CB), 0, s, a);
     else if (a.aa == 2) hipLaunchKernelGGL((k_collide<L, COLL, S, false, 2>), dim3(nb), dim3(CB), 0, s, a);
     else if (noisy(a)) {
       // inflow noise on the moving-wall links: separate instantiations, so
