@@ -261,9 +261,13 @@ __device__ inline void gather_row(const S *fin, const S *gin, const int32_t *xnb
 // regular-pull mask), so the wavefront does not run a second, serial
 // gather for them.  The multi-speed lattices keep the split: there the
 // bulk values held across the row reads cost registers (D2Q37: 167 -> 193
-// VGPRs, one wavefront per SIMD fewer) and time.
+// VGPRs, one wavefront per SIMD fewer) and time.  SPL: D2Q9 grids of a
+// few fillings of the chip (Topo::split) split too: their launches are one
+// chain of dependent reads, which the mask lengthens by a round trip (64 x 64
+// cavity, 20 steps: 419 -> 384 us).
 // nbs must be a staged table: gather_one reads exception rows itself.
-template <class L, class S, bool PRE, bool DDF, int AA = 0, bool NZ = true, bool RAW = false, bool O32 = false>
+template <class L, class S, bool PRE, bool DDF, int AA = 0, bool NZ = true, bool RAW = false, bool O32 = false,
+          bool SPL = false>
 __device__ inline void gather(const S *fin, const S *gin, const Topo &tp, const uint32_t *nbs, int64_t vbase, int64_t c, int lane, int32_t brick, uint64_t xm,
                               const double (&uw)[6][3], double cs2w, typename Sto<S>::C *f,
                               typename Sto<S>::C *g) {
@@ -272,7 +276,7 @@ __device__ inline void gather(const S *fin, const S *gin, const Topo &tp, const 
   const int64_t c0 = pix<L::Q>(0, c);
   f[0] = RAW ? Sto<S>::ldr(fin[c0]) : Sto<S>::ld(fin, c0, L::S.w[0]);
   if (DDF) g[0] = Sto<S>::ld(gin, c0, 0.0);
-  constexpr bool UNI = !PRE && AA == 0 && L::B == 1;
+  constexpr bool UNI = !PRE && AA == 0 && L::B == 1 && !SPL;
   const bool ex = (xm >> lane) & 1ull;
   if (UNI || !ex) {
     if (PRE) {
@@ -1100,7 +1104,7 @@ __device__ inline void explode_store(const KArgs &a, void *ef, void *eg, const S
 // XCD dispatch keeps its per-XCD contiguous order inside the level; a block
 // takes its level's buffers, cell range and relaxation time from the table
 // and runs the same update as a per-level launch.
-template <class L, int COLL, class S, bool PRE, int AA = 0, bool NZ = false, bool O32 = false>
+template <class L, int COLL, class S, bool PRE, int AA = 0, bool NZ = false, bool O32 = false, bool SPL = false>
 __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
     __attribute__((amdgpu_waves_per_eu(MinWaves<L, COLL, S>::value))) k_collide(const KArgs a) {
   using C = typename Sto<S>::C;
@@ -1168,7 +1172,7 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
   // and the moments and the regularised populations are formed from the
   // small deviations instead of from f_i ~ w_i
   constexpr bool SH = std::is_same<S, __half>::value && COLL == COLL_RR && product_basis<L>();
-  gather<L, S, PRE || AA == 1, DDF, AA == 2 ? 2 : 0, NZ, SH, O32>(fin, gin, a.topo, nbs[0], a.vbase, c, threadIdx.x & 63, brick, xm,
+  gather<L, S, PRE || AA == 1, DDF, AA == 2 ? 2 : 0, NZ, SH, O32, SPL>(fin, gin, a.topo, nbs[0], a.vbase, c, threadIdx.x & 63, brick, xm,
                                                        a.ph.uw, a.ph.cs2w, f, g);
   if (!(fl & (F_FINE_GHOST | F_BC_NEUMANN | F_BC_EQ))) {
     C rho, u[3], T = (C)0, rho1 = (C)0;
@@ -1850,6 +1854,20 @@ template <class L, int COLL, class S>
 struct Launch {
   static constexpr bool DDF = COLL >= COLL_DDF_POLY;
   static constexpr bool LAM = COLL >= COLL_DDF_NEWTON;
+  // the steady-state two-buffer collide of `grid` blocks
+  template <bool NZ>
+  static void steady(const KArgs &a, dim3 grid, hipStream_t s) {
+    constexpr int CB = CollideBlock<L, COLL>::value;
+    // a split grid's buffers are far below 4 GB
+    if constexpr (L::D == 2 && L::B == 1) {
+      if (a.topo.split) {
+        hipLaunchKernelGGL((k_collide<L, COLL, S, false, 0, NZ, true, true>), grid, dim3(CB), 0, s, a);
+        return;
+      }
+    }
+    if (a.topo.off32) hipLaunchKernelGGL((k_collide<L, COLL, S, false, 0, NZ, true>), grid, dim3(CB), 0, s, a);
+    else hipLaunchKernelGGL((k_collide<L, COLL, S, false, 0, NZ>), grid, dim3(CB), 0, s, a);
+  }
   static void collide(const KArgs &a, bool pre, hipStream_t s) {
     if (a.count <= 0) return;
     constexpr int CB = CollideBlock<L, COLL>::value;
@@ -1862,23 +1880,18 @@ struct Launch {
       // that the others keep their registers
       if constexpr (COLL < COLL_DDF_NEWTON) {
         if (pre) hipLaunchKernelGGL((k_collide<L, COLL, S, true, 0, true>), dim3(nb), dim3(CB), 0, s, a);
-        else if (a.topo.off32) hipLaunchKernelGGL((k_collide<L, COLL, S, false, 0, true, true>), dim3(nb), dim3(CB), 0, s, a);
-        else hipLaunchKernelGGL((k_collide<L, COLL, S, false, 0, true>), dim3(nb), dim3(CB), 0, s, a);
+        else steady<true>(a, dim3(nb), s);
       }
     } else if (pre) hipLaunchKernelGGL((k_collide<L, COLL, S, true>), dim3(nb), dim3(CB), 0, s, a);
-    else if (a.topo.off32) hipLaunchKernelGGL((k_collide<L, COLL, S, false, 0, false, true>), dim3(nb), dim3(CB), 0, s, a);
-    else hipLaunchKernelGGL((k_collide<L, COLL, S, false>), dim3(nb), dim3(CB), 0, s, a);
+    else steady<false>(a, dim3(nb), s);
   }
   static bool noisy(const KArgs &a) { return a.topo.xdu != nullptr; }
   static void collide_multi(const KArgs &a, hipStream_t s) {
     if constexpr (COLL < COLL_DDF_NEWTON) {
-      constexpr int CB = CollideBlock<L, COLL>::value;
       const dim3 grid((unsigned)a.multi.block0[a.multi.n]);
       if (a.multi.n > 0 && a.multi.block0[a.multi.n] > 0) {
-        if (noisy(a) && a.topo.off32) hipLaunchKernelGGL((k_collide<L, COLL, S, false, 0, true, true>), grid, dim3(CB), 0, s, a);
-        else if (noisy(a)) hipLaunchKernelGGL((k_collide<L, COLL, S, false, 0, true>), grid, dim3(CB), 0, s, a);
-        else if (a.topo.off32) hipLaunchKernelGGL((k_collide<L, COLL, S, false, 0, false, true>), grid, dim3(CB), 0, s, a);
-        else hipLaunchKernelGGL((k_collide<L, COLL, S, false>), grid, dim3(CB), 0, s, a);
+        if (noisy(a)) steady<true>(a, grid, s);
+        else steady<false>(a, grid, s);
       }
     }
   }

@@ -64,6 +64,7 @@ struct Topo {
   const uint64_t *xreg;    // [rows] bit i: the row's source of population i is the bulk gather's
   int64_t xstride;
   const double *xdu;       // [Q-1][xstride] xi_i . (inflow noise) of the rows, or null
+  int split;               // exception lanes read all sources from their rows (small 2-D grids)
   int off32;               // population buffers under 4 GB: the steady-state pull uses 32-bit byte offsets
 };
 
