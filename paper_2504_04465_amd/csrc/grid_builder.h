@@ -20,6 +20,7 @@ enum NodeFlag : uint8_t {
   F_SPONGE = 16,
   F_MOVING = 32,  // device copy only: a population comes from a moving wall
   F_HOLE = 64,    // device copy only: a slot of a brick without a cell
+  F_BC_SOURCE = 128,  // device copy only: Neumann cells copy this cell (FillTable)
 };
 
 enum { NBR_NONE = -1, NBR_SOLID = -2 };  // moving wall on face k: -3 - k

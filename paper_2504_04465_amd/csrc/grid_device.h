@@ -75,6 +75,9 @@ int fetch_host_layout(const DeviceGridArrays &dg, DeviceLayout *y, hipStream_t s
 // pulled from a moving wall, F_HOLE for slots without a cell
 void launch_slot_flags(const DeviceGridArrays &dg, int64_t nslot, uint8_t *out, hipStream_t stream);
 
+// flags[slot[k]] |= bit for m distinct slots
+void launch_mark_slots(const int32_t *slot, int64_t m, uint8_t bit, uint8_t *flags, hipStream_t stream);
+
 // remesh_sources on the device: for every cell of `nw` its sources among
 // the flow cells (not fine ghosts) of `old`, same order and weights value
 // for value, from the two grids' kept device tables (coordinates, levels,

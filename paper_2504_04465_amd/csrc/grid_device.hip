@@ -1434,6 +1434,16 @@ __global__ void k_slot_flags(int64_t n, int Qm, const uint8_t *flag, const int32
 }
 }  // namespace
 
+namespace {
+__global__ void k_mark_slots(const int32_t *slot, int64_t m, uint8_t bit, uint8_t *flags) {
+  GRID_STRIDE(k, m) flags[slot[k]] |= bit;
+}
+}  // namespace
+
+void launch_mark_slots(const int32_t *slot, int64_t m, uint8_t bit, uint8_t *flags, hipStream_t st) {
+  if (m > 0) hipLaunchKernelGGL(k_mark_slots, dim3(grid_for(m)), dim3(TPB), 0, st, slot, m, bit, flags);
+}
+
 void launch_slot_flags(const DeviceGridArrays &dg, int64_t nslot, uint8_t *out, hipStream_t st) {
   hipMemsetAsync(out, F_HOLE, std::max<int64_t>(nslot, 1), st);
   if (dg.n > 0)

@@ -84,6 +84,8 @@ struct lbm_ctx {
   uint64_t *d_unknown = nullptr;
   int32_t *d_bc_cell = nullptr, *d_bc_src = nullptr;
   int8_t *d_bc_face = nullptr;
+  FillTable fill{};             // Neumann cells by source (off null: the boundary kernel fills them)
+  bool eq_cells[8]{};           // equilibrium boundary cells on the level
   unsigned long long *d_counters = nullptr;
   double *d_scratch = nullptr;
   size_t scratch_bytes = 0;
@@ -169,6 +171,7 @@ void free_device(lbm_ctx *c) {
   c->d_unknown = nullptr;
   c->d_bc_cell = c->d_bc_src = nullptr;
   c->d_bc_face = nullptr;
+  c->fill = FillTable{};
   c->d_counters = nullptr;
   c->d_scratch = nullptr;
   c->scratch_bytes = 0;
@@ -329,8 +332,9 @@ FaceVals face_vals(const lbm_ctx *c) {
 
 void launch_bcfill(lbm_ctx *c, int l) {
   const int64_t cnt = c->g.boff[l + 1] - c->g.boff[l];
-  if (cnt <= 0) return;
+  if (cnt <= 0 || (c->fill.off && !c->eq_cells[l])) return;
   BArgs a{};
+  a.skip_neumann = c->fill.off != nullptr;
   a.f = const_cast<void *>(fbuf(c, l));
   a.g = const_cast<void *>(gbuf(c, l));
   a.lam = c->d_lam;
@@ -389,6 +393,7 @@ KArgs collide_args(lbm_ctx *c, int l, int par) {
   a.gslot = c->d_gslot;
   a.xghost = c->d_xghost;
   a.child = c->d_child;
+  a.fill = c->fill;
   return a;
 }
 
@@ -545,6 +550,53 @@ lbm_status host_tables(lbm_ctx *c) {
   std::string err;
   if (fetch_host_grid(c->dg, &c->g, c->stream, &err) != 0 || fetch_host_layout(c->dg, &c->lay, c->stream, &err) != 0)
     return set_err(c, LBM_E_DEVICE, err);
+  return LBM_OK;
+}
+
+// the Neumann cells by their source cells (FillTable), and the sources' flags
+lbm_status build_fill(lbm_ctx *c) {
+  const int64_t nbc = c->g.boff[c->L];
+  for (int l = 0; l < c->L; ++l) c->eq_cells[l] = false;
+  if (!c->ops.fills || c->p.in_place || nbc == 0) return LBM_OK;
+  std::vector<int32_t> cell(nbc), src(nbc);
+  std::vector<int8_t> face(nbc);
+  HIP_TRY(c, hipMemcpyAsync(cell.data(), c->d_bc_cell, sizeof(int32_t) * nbc, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(src.data(), c->d_bc_src, sizeof(int32_t) * nbc, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipMemcpyAsync(face.data(), c->d_bc_face, nbc, hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
+  std::vector<uint64_t> pairs;  // source, cell
+  pairs.reserve(nbc);
+  for (int l = 0; l < c->L; ++l)
+    for (int64_t k = c->g.boff[l]; k < c->g.boff[l + 1]; ++k) {
+      if (c->face[face[k]].kind == LBM_BC_EQUILIBRIUM) c->eq_cells[l] = true;
+      else pairs.push_back((uint64_t)(uint32_t)src[k] << 32 | (uint32_t)cell[k]);
+    }
+  if (pairs.empty()) return LBM_OK;
+  std::sort(pairs.begin(), pairs.end());
+  std::vector<uint64_t> mask(c->NS / 64, 0ull);
+  std::vector<int32_t> base(c->NS / 64, 0), off, to(pairs.size()), from;
+  for (size_t k = 0; k < pairs.size(); ++k) {
+    const int32_t s = (int32_t)(pairs[k] >> 32);
+    to[k] = (int32_t)(uint32_t)pairs[k];
+    if (!from.empty() && from.back() == s) continue;
+    if (!mask[s / 64]) base[s / 64] = (int32_t)from.size();
+    mask[s / 64] |= 1ull << (s & 63);
+    from.push_back(s);
+    off.push_back((int32_t)k);
+  }
+  off.push_back((int32_t)pairs.size());
+  lbm_status s;
+  uint64_t *d_mask = nullptr;
+  int32_t *d_base = nullptr, *d_off = nullptr, *d_to = nullptr, *d_from = nullptr;
+  if ((s = upload(c, &d_mask, mask.data(), mask.size())) != LBM_OK) return s;
+  if ((s = upload(c, &d_base, base.data(), base.size())) != LBM_OK) return s;
+  if ((s = upload(c, &d_off, off.data(), off.size())) != LBM_OK) return s;
+  if ((s = upload(c, &d_to, to.data(), to.size())) != LBM_OK) return s;
+  if ((s = upload(c, &d_from, from.data(), from.size())) != LBM_OK) return s;
+  launch_mark_slots(d_from, (int64_t)from.size(), F_BC_SOURCE, c->d_flags, c->stream);
+  if ((s = check_launch(c)) != LBM_OK) return s;
+  dev_release(c, d_from);
+  c->fill = FillTable{d_mask, d_base, d_off, d_to};
   return LBM_OK;
 }
 
@@ -875,6 +927,7 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
   (void)NCH;
   c->d_counters = (unsigned long long *)dev_alloc(c, sizeof(unsigned long long) * CNT_COUNT * CNT_COPIES);
   if (!c->d_counters) return set_err(c, LBM_E_NOMEM, "counter allocation failed");
+  if ((s = build_fill(c)) != LBM_OK) return s;
   HIP_TRY(c, hipMemset(c->d_counters, 0, sizeof(unsigned long long) * CNT_COUNT * CNT_COPIES));
   return LBM_OK;
 }

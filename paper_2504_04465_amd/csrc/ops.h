@@ -68,6 +68,15 @@ struct Topo {
   int off32;               // population buffers under 4 GB: the steady-state pull uses 32-bit byte offsets
 };
 
+// Neumann cells filled by the collide of their source: the k-th source cell
+// of its brick (k = set bits of mask[brick] below its lane) is copied to the
+// slots cell[off[j] .. off[j + 1]), j = base[brick] + k.  off null: the
+// boundary kernel fills them.
+struct FillTable {
+  const uint64_t *mask;
+  const int32_t *base, *off, *cell;
+};
+
 // the collides of every level active at a substep in one launch: what
 // differs between the levels (the rest of KArgs is common to them)
 constexpr int MAX_LEVELS = 8;
@@ -110,6 +119,7 @@ struct KArgs {
   const int32_t *xghost, *child;
   void *ef, *eg;
   int skip_fg;
+  FillTable fill;
   MultiTable multi;    // n > 0: every active level of a substep in one launch
 };
 
@@ -178,6 +188,7 @@ struct BArgs {
   // them: rows opp(i) (mode 1), or pushed through its exception row
   // bc_row[k] (mode 2)
   int mode;
+  int skip_neumann;    // the collide has filled those
   const int32_t *stage, *bc_row;
   const int32_t *xnbr;
   int64_t xstride;
@@ -227,6 +238,7 @@ struct Ops {
   // two buffers); null where the model keeps per-level launches
   void (*collide_multi)(const KArgs &, hipStream_t);
   int collide_block;        // threads per collide block
+  bool fills;               // the two-buffer collide fills the Neumann cells
   void (*coalesce)(const CArgs &, bool pre_child, hipStream_t);
   void (*explode)(const EArgs &, hipStream_t);
   void (*bcfill)(const BArgs &, hipStream_t);
