@@ -992,6 +992,18 @@ struct MinWaves {
   static constexpr int value = COLL < COLL_DDF_POLY ? (sizeof(S) == 8 ? 4 : 6) : (COLL >= COLL_DDF_NEWTON ? 2 : 1);
 };
 
+// Whether the Newton collide parks f and g in LDS during the solve, or pulls
+// them again after it.  Parked D2Q21 FP64 populations take 86 KB a block,
+// one wavefront per SIMD; pulled again, two (two steps of a 400 x 400 tube:
+// 170 -> 158 us, of an airfoil 512 x 256: 871 -> 810).  Where two blocks fit
+// in the LDS anyway, neither way is measurably better (D2Q13 FP64: 115 to
+// 118 us both) and parking reads less; D2Q37 FP64 spills at two wavefronts
+// (340 against 258 us).
+template <class L, class C>
+constexpr bool newton_park() {
+  return 2 * L::Q * sizeof(C) * BLOCK <= 80 * 1024 || L::Q > 21;
+}
+
 // Block size of the collide kernel: four bricks (256 threads) on every
 // lattice.  With the chunked population layout this beats the 2 x 2 x 2
 // cube of bricks that is consecutive in Z order (512 threads; sphere FP16
@@ -1267,22 +1279,31 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
       }
       int it;
       if constexpr (COLL >= COLL_DDF_NEWTON) {
-        // park f and g in LDS while the Newton solve needs the registers
-        // (the memory clobbers keep the compiler from holding them anyway)
-        __shared__ C park[BLOCK / 64][2 * Q][64];
-        const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
+        if constexpr (newton_park<L, C>()) {
+          // park f and g in LDS while the Newton solve needs the registers
+          // (the memory clobbers keep the compiler from holding them anyway)
+          __shared__ C park[BLOCK / 64][2 * Q][64];
+          const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-          park[wv][i][ln] = f[i];
-          park[wv][Q + i][ln] = g[i];
-        }
-        asm volatile("" ::: "memory");
-        it = equilibrium_any<L, COLL, C>(rhop, u, T, a.ph, lam, a.ph.warm != 0, feq, geq, etab);
-        asm volatile("" ::: "memory");
+          for (int i = 0; i < Q; ++i) {
+            park[wv][i][ln] = f[i];
+            park[wv][Q + i][ln] = g[i];
+          }
+          asm volatile("" ::: "memory");
+          it = equilibrium_any<L, COLL, C>(rhop, u, T, a.ph, lam, a.ph.warm != 0, feq, geq, etab);
+          asm volatile("" ::: "memory");
 #pragma unroll
-        for (int i = 0; i < Q; ++i) {
-          f[i] = park[wv][i][ln];
-          g[i] = park[wv][Q + i][ln];
+          for (int i = 0; i < Q; ++i) {
+            f[i] = park[wv][i][ln];
+            g[i] = park[wv][Q + i][ln];
+          }
+        } else {
+          // pulled again, from the caches
+          it = equilibrium_any<L, COLL, C>(rhop, u, T, a.ph, lam, a.ph.warm != 0, feq, geq, etab);
+          asm volatile("" ::: "memory");
+          gather<L, S, PRE || AA == 1, DDF, AA == 2 ? 2 : 0, NZ, SH, O32>(fin, gin, a.topo, nbs[0], a.vbase, c,
+                                                                          threadIdx.x & 63, brick, xm, a.ph.uw,
+                                                                          a.ph.cs2w, f, g);
         }
       } else {
         it = equilibrium_any<L, COLL, C>(rhop, u, T, a.ph, lam, a.ph.warm != 0, feq, geq);
