@@ -129,3 +129,38 @@ def test_device_grid_run_and_remesh_bit_identical():
     say(f"[remesh] vortex 256: device {times[-1][0] * 1e3:.1f} ms, host {times[-1][1] * 1e3:.1f} ms")
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("ext", [(1, 1), (31, 33), (32, 64), (97, 5), (3, 130), (1, 1, 1), (7, 9, 8), (8, 8, 16),
+                                 (17, 2, 41), (21, 19, 24)], ids=lambda e: "x".join(map(str, e)))
+def test_device_order_at_tile_edges(ext):
+    """the cells' Z order is made from sorted 32 x 32 (8 x 8 x 8) tiles:
+    extents at, below and above a tile, one refined window off the tiles'
+    grid where it fits, solid cells in between"""
+    D = len(ext)
+    rng = np.random.default_rng(sum(ext))
+    lo = tuple(min(5, e // 3) for e in ext)
+    n = tuple(max(e - 2 * o, 0) for e, o in zip(ext, lo))
+    levels = 2 if min(n) >= 6 and min(lo) >= 1 else 1
+    solid = []
+    for l in range(levels):
+        e = [x << l for x in ext]
+        m = rng.random(e[::-1]) < 0.2
+        if levels == 2:  # a solid may not cut the interface: clear of its ghosts
+            for a in range(D):
+                i = np.arange(e[a])
+                d = np.minimum(np.abs(i - (lo[a] << l)), np.abs(i - ((lo[a] + n[a]) << l)))
+                m &= (d >= (6 << l)).reshape([-1 if b == D - 1 - a else 1 for b in range(D)])
+        m.flat[0] = False
+        solid.append(W.Mask(m.astype(np.uint8), (0,) * D))
+    refine = [W.Mask(np.ones(n[::-1], np.uint8), lo)] if levels == 2 else []
+    faces = [W.Face("wall") for _ in range(2 * D)]
+    sims = []
+    for device in (True, False):
+        s = B.LBM("D2Q9" if D == 2 else "D3Q27", "RR", "fp32", nu_finest=0.01, T0=1.0 / 3.0)
+        s.device_build(device)
+        s.grid(D, ext, levels, refine, solid, faces)
+        sims.append(s)
+    same_grid(*sims, ext)
+    for s in sims:
+        s.close()
