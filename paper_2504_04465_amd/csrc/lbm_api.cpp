@@ -214,7 +214,12 @@ template <class T>
 lbm_status upload(lbm_ctx *c, T **dst, const T *src, size_t count) {
   *dst = (T *)dev_alloc(c, count * sizeof(T));
   if (!*dst) return set_err(c, LBM_E_NOMEM, "device allocation failed");
-  if (count) HIP_TRY(c, hipMemcpy(*dst, src, count * sizeof(T), hipMemcpyHostToDevice));
+  if (count) {
+    // on the context's stream: kernels queued there may still read or write
+    // the memory that the allocation has just been given
+    HIP_TRY(c, hipMemcpyAsync(*dst, src, count * sizeof(T), hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));  // the host array is the caller's
+  }
   return LBM_OK;
 }
 
@@ -928,7 +933,8 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
   c->d_counters = (unsigned long long *)dev_alloc(c, sizeof(unsigned long long) * CNT_COUNT * CNT_COPIES);
   if (!c->d_counters) return set_err(c, LBM_E_NOMEM, "counter allocation failed");
   if ((s = build_fill(c)) != LBM_OK) return s;
-  HIP_TRY(c, hipMemset(c->d_counters, 0, sizeof(unsigned long long) * CNT_COUNT * CNT_COPIES));
+  // (stream order, as in upload; a grid build is never captured)
+  HIP_TRY(c, hipMemsetAsync(c->d_counters, 0, sizeof(unsigned long long) * CNT_COUNT * CNT_COPIES, c->stream));
   return LBM_OK;
 }
 
@@ -1110,7 +1116,8 @@ lbm_status lbm_remesh(lbm_ctx *c, const lbm_mask *refine, const lbm_mask *solid)
   std::vector<float> mlpw;
   if (c->have_mlp) {
     mlpw.resize(MLP_PARAMS);
-    HIP_TRY(c, hipMemcpy(mlpw.data(), c->d_mlp_w, sizeof(float) * MLP_PARAMS, hipMemcpyDeviceToHost));
+    HIP_TRY(c, hipMemcpyAsync(mlpw.data(), c->d_mlp_w, sizeof(float) * MLP_PARAMS, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
   // 1. the old tree's synchronisation-point state, canonical [rows][n_old],
   //    in a buffer of its own (the new grid releases the context's memory)
@@ -1753,7 +1760,8 @@ lbm_status lbm_mlp_train(lbm_ctx *c, const double *x, const double *lambda, int6
       const double lim = 0.5 * std::sqrt(6.0 / fan[k]);
       for (int q = 0; q < cnt[k]; ++q) w[offs[k] + q] = (float)(lim * U(rng));
     }
-    HIP_TRY(c, hipMemcpy(c->d_mlp_w, w.data(), sizeof(float) * MLP_PARAMS, hipMemcpyHostToDevice));
+    HIP_TRY(c, hipMemcpyAsync(c->d_mlp_w, w.data(), sizeof(float) * MLP_PARAMS, hipMemcpyHostToDevice, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
   // canonical octant, output normalisation from the labels, normalised
   // samples: on the device, while the host shuffles the first epoch
