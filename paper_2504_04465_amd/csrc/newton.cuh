@@ -34,7 +34,7 @@ namespace lbm {
 // exponential: exp(-s) = 2^n 2^(j/64) exp(r), 64 n + j = rint(-64 s / ln 2),
 // |r| <= ln 2 / 128.  The Taylor polynomial of degree five leaves
 // r^6 / 720 < 4e-17 relative; the argument reduction uses ln 2 / 64 in two
-// parts.  16 vector instructions and one table read where the library's
+// parts.  15 vector instructions and one table read where the library's
 // exponential takes about twice as many.  n is clamped to the exponent range
 // (the results there are of the order of 1e-308 and 1e308).
 // ---------------------------------------------------------------------------
@@ -69,11 +69,7 @@ __device__ inline double exp_neg(double s, const double *tab) {
   constexpr double magic = 6755399441055744.0;  // 1.5 2^52: the sum's low bits are the rounded integer
   const double t = __builtin_fma(s, -0x1.71547652b82fep+6, magic);
   const double kf = t - magic;
-  // the rounded integer, saturated: the low bits of t would be free but wrap
-  // from s = 2e7 on, where a trial step of a solve that diverges may well be
-  // (the conversion costs the D2Q21 collide 0.4 %)
-  int k;
-  asm("v_cvt_i32_f64 %0, %1" : "=v"(k) : "v"(kf));
+  const int k = (int)(uint32_t)__builtin_bit_cast(uint64_t, t);
   double r = __builtin_fma(kf, -0x1.62e42fc000000p-7, -s);
   r = __builtin_fma(kf, -0x1.7d1cf79abc9e4p-34, r);
   double q = __builtin_fma(r, 1.0 / 120.0, 1.0 / 24.0);
