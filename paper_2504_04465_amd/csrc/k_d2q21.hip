@@ -92,7 +92,9 @@ __global__ void __launch_bounds__(BLOCK) k_collide_mlp(const KArgs a) {
     } else {
       // the network's multipliers as they are
       MomSums m;
-      expo_sums<L, C>(lam, etab, m, e);
+      // (in FP32 the table's remainders round away, and their registers would
+      // cost a wavefront: 1347 -> 1573 us a pass of the surrogate alone)
+      expo_sums<L, C, (sizeof(C) == 8)>(lam, etab, m, e);
     }
     C feq[Q], geq[Q];
     const C kg = ((C)2 * (C)a.ph.Cv - (C)L::D) * T;
