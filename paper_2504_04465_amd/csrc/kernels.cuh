@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "grid_builder.h"
+#include "inplace.h"
 #include "lattice.h"
 #include "ops.h"
 #include "newton.cuh"
@@ -176,6 +177,11 @@ __device__ inline int64_t pix(int64_t i, int64_t s) {
   return (((s >> PCH_SH) * Q + i) << PCH_SH) + (s & (PCH - 1));
 }
 
+template <int Q>
+__device__ inline int64_t pix(const Word &w) {
+  return pix<Q>(w.row, w.slot);
+}
+
 // offset of brick b's population-0 row in units of 64 values (32 bits for
 // any buffer of fewer than 2^38 / Q slots)
 template <int Q>
@@ -206,8 +212,9 @@ __device__ inline int lane_bits(int p, int d) {
 // source is loaded before any is used, so the loads overlap.
 // Populations not in `want` (bit i) are neither loaded nor set.
 // AA = 2: the single in-place buffer after an even step holds cell x's
-// post-collision population i in row opp(i); pulls swap the rows (a wall
-// returns the cell's own row i).
+// post-collision population i in row opp(i); pulls swap the rows (odd_pull:
+// a wall returns the cell's own row i, which also holds a population that
+// the cell keeps).
 //
 // RAW: FP16 storage only, the populations are returned as stored (f_i - w_i);
 // the moving-wall term is the same in that representation.
@@ -225,9 +232,9 @@ __device__ inline void gather_row(const S *fin, const S *gin, const int32_t *xnb
     if (!((want >> i) & 1ull)) continue;
     const int32_t s = sv[i];
     int64_t idx;
-    const int ri = AA == 2 ? L::S.opp[i] : i, ro = AA == 2 ? i : L::S.opp[i];
     if (PRE) idx = pix<L::Q>(i, (int64_t)s >= vbase ? (int64_t)s : c);
-    else idx = s >= 0 ? pix<L::Q>(ri, s) : pix<L::Q>(ro, c);
+    else if (AA == 2) idx = pix<L::Q>(odd_pull(i, L::S.opp[i], s, (int32_t)c));
+    else idx = s >= 0 ? pix<L::Q>(i, s) : pix<L::Q>(L::S.opp[i], c);
     // the lattice is symmetric: w of the opposite population is w_i
     f[i] = RAW ? Sto<S>::ldr(fin[idx]) : Sto<S>::ld(fin, idx, L::S.w[i]);
     if (DDF) g[i] = Sto<S>::ld(gin, idx, 0.0);
@@ -404,26 +411,39 @@ __device__ inline void push_store(S *fout, S *gout, const Topo &tp, const uint32
     for (int i = 1; i < L::Q; ++i) {
       const int j = L::S.opp[i];
       const int32_t s = tp.xnbr[(int64_t)(j - 1) * tp.xstride + row];
-      // a population the cell pulls from itself (a fine ghost at the edge of
-      // its level keeps it) is stored in its own row; nobody pulls from a
-      // cell's own slot through the opposite link, so that push is dropped
-      if (tp.xnbr[(int64_t)(i - 1) * tp.xstride + row] == (int32_t)c) {
+      if (keeps(tp.xnbr[(int64_t)(i - 1) * tp.xstride + row], (int32_t)c)) {
         Sto<S>::stn(fout, pix<L::Q>(i, c), f[i], RAW ? 0.0 : L::S.w[i]);
         if (DDF) Sto<S>::stn(gout, pix<L::Q>(i, c), g[i], 0.0);
       }
-      if (s == (int32_t)c) continue;
-      if (s >= 0) {
-        Sto<S>::stn(fout, pix<L::Q>(i, s), f[i], RAW ? 0.0 : L::S.w[i]);
-        if (DDF) Sto<S>::stn(gout, pix<L::Q>(i, s), g[i], 0.0);
-      } else {
+      const Word to = odd_store(i, j, s, (int32_t)c);
+      if (to.row == i) {
+        Sto<S>::stn(fout, pix<L::Q>(i, to.slot), f[i], RAW ? 0.0 : L::S.w[i]);
+        if (DDF) Sto<S>::stn(gout, pix<L::Q>(i, to.slot), g[i], 0.0);
+      } else if (to.row == j) {
         C v = f[i];
         if (s <= -2)
           v += (C)(2.0 * L::S.w[j] * wall_dot<L>(uw, -2 - s, j) / cs2w);  // no inflow noise in place
-        Sto<S>::stn(fout, pix<L::Q>(j, c), v, RAW ? 0.0 : L::S.w[j]);
-        if (DDF) Sto<S>::stn(gout, pix<L::Q>(j, c), g[i], 0.0);
+        Sto<S>::stn(fout, pix<L::Q>(j, to.slot), v, RAW ? 0.0 : L::S.w[j]);
+        if (DDF) Sto<S>::stn(gout, pix<L::Q>(j, to.slot), g[i], 0.0);
       }
     }
   }
+}
+
+// After the rows of an even step (row opp(i) holds population i): the
+// populations that cell c keeps, each in its own row (even_store).  Only fine
+// ghosts and boundary cells have any.
+template <class L, class S, bool DDF, bool RAW>
+__device__ inline void keep_store(S *fout, S *gout, const Topo &tp, int64_t c, const typename Sto<S>::C *f,
+                                  const typename Sto<S>::C *g) {
+  // the mask is read again rather than held across the collision
+  const uint64_t kept = tp.xkeep[tp.xbase[c >> 6] + __popcll(tp.xmask[c >> 6] & ((1ull << (c & 63)) - 1ull))];
+#pragma unroll
+  for (int i = 1; i < L::Q; ++i)
+    if ((kept >> i) & 1ull) {
+      Sto<S>::st(fout, pix<L::Q>(i, c), f[i], RAW ? 0.0 : L::S.w[i]);
+      if (DDF) Sto<S>::st(gout, pix<L::Q>(i, c), g[i], 0.0);
+    }
 }
 
 // Gather for one cell anywhere (no brick per wavefront): the neighbour
@@ -1366,6 +1386,10 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
       }
     }
   }
+  if constexpr (AA == 1) {
+    if (fl & (F_FINE_GHOST | F_BC_NEUMANN | F_BC_EQ))
+      keep_store<L, S, DDF, SH>(fout, gout, a.topo, c, f, g);
+  }
   if constexpr (FILL) {
     if ((fl & F_BC_SOURCE) && a.fill.off) fill_store<L, S, DDF, SH>(a.fill, fout, gout, c, f, g);
   }
@@ -1433,9 +1457,9 @@ __global__ void __launch_bounds__(BLOCK) k_coalesce(const CArgs a) {
     if (DDF) vg[k] = (C)0;
     if (i >= L::Q || !((mask >> i) & 1ull) || ch < 0) continue;
     int64_t idx;
-    const int64_t ri = AAF == 2 ? L::S.opp[i] : i, ro = AAF == 2 ? i : L::S.opp[i];
     if (PRE) idx = pix<L::Q>(i, (int64_t)sv[k] >= a.vbase ? (int64_t)sv[k] : (int64_t)ch);
-    else idx = sv[k] >= 0 ? pix<L::Q>(ri, sv[k]) : pix<L::Q>(ro, ch);
+    else if (AAF == 2) idx = pix<L::Q>(odd_pull(i, L::S.opp[i], sv[k], ch));
+    else idx = sv[k] >= 0 ? pix<L::Q>(i, sv[k]) : pix<L::Q>(L::S.opp[i], ch);
     v[k] = Sto<S>::ld(fin, idx, L::S.w[i]);
     if (DDF) vg[k] = Sto<S>::ld(gin, idx, 0.0);
   }
@@ -1470,10 +1494,11 @@ __global__ void __launch_bounds__(BLOCK) k_coalesce(const CArgs a) {
 // place: with two buffers the collide stores them (explode_store).  The
 // ghost's populations are read from its coalesced slot, where its collide
 // left them; MODE 1 (fine level at an odd phase): child row opp(i)
-// takes population i; MODE 2 (even phase): population i goes to row i of
-// the cell that pulls it from the child, as the child's own push would have
-// sent it (a wall returns it to the child's row opp(i) with the moving-wall
-// term; a population the child pulls from itself stays in its row i).
+// takes population i (even_store); MODE 2 (even phase): population i goes to
+// row i of the cell that pulls it from the child, as the child's own push
+// would have sent it (a wall returns it to the child's row opp(i) with the
+// moving-wall term).  In both a population that the child keeps goes to its
+// row i, and the lane of population opp(i) leaves that row alone.
 template <int POPS, class L, class S, bool DDF, bool LAM, int MODE>
 __global__ void __launch_bounds__(BLOCK) k_explode(const EArgs a) {
   using C = typename Sto<S>::C;
@@ -1489,7 +1514,8 @@ __global__ void __launch_bounds__(BLOCK) k_explode(const EArgs a) {
   const S *fin = (const S *)a.fin_coarse;
   S *fout = (S *)a.fout_fine;
   S *gout = (S *)a.gout_fine;
-  const int64_t crow = MODE == 2 ? (int64_t)a.crow[gk * NCH + (t % NCH)] : 0;
+  const int64_t crow = a.crow[gk * NCH + (t % NCH)];
+  const uint64_t kept = a.xkeep[crow];
   const int i0 = (int)blockIdx.y * POPS;
   S vs[POPS], vgs[DDF ? POPS : 1];
 #pragma unroll
@@ -1503,28 +1529,27 @@ __global__ void __launch_bounds__(BLOCK) k_explode(const EArgs a) {
     const int i = i0 + k;
     if (i >= L::Q) break;
     const S v = vs[k], vg = DDF ? vgs[k] : S();
-    if (MODE != 2 || i == 0) {
-      const int64_t r = MODE == 1 ? L::S.opp[i] : i;
-      fout[pix<L::Q>(r, ch)] = v;
-      if (DDF) gout[pix<L::Q>(r, ch)] = vg;
+    if (i == 0) {
+      fout[pix<L::Q>(0, ch)] = v;
+      if (DDF) gout[pix<L::Q>(0, ch)] = vg;
       continue;
     }
     const int j = L::S.opp[i];
-    if (a.xnbr[(int64_t)(i - 1) * a.xstride + crow] == ch) {
+    if ((kept >> i) & 1ull) {
       fout[pix<L::Q>(i, ch)] = v;
       if (DDF) gout[pix<L::Q>(i, ch)] = vg;
     }
-    const int32_t s = a.xnbr[(int64_t)(j - 1) * a.xstride + crow];
-    if (s == ch) continue;
-    if (s >= 0) {
-      fout[pix<L::Q>(i, s)] = v;
-      if (DDF) gout[pix<L::Q>(i, s)] = vg;
+    const int32_t s = MODE == 1 ? -1 : a.xnbr[(int64_t)(j - 1) * a.xstride + crow];
+    const Word to = MODE == 1 ? even_store(j, (kept >> j) & 1ull ? ch : -1, ch) : odd_store(i, j, s, ch);
+    if (to.row < 0) continue;
+    if (MODE == 1 || s >= 0) {
+      fout[pix<L::Q>(to)] = v;
     } else {
       C w = Sto<S>::ldv(v, L::S.w[i]);
       if (s <= -2) w += (C)(2.0 * L::S.w[j] * wall_dot<L>(a.uw, -2 - s, j) / a.cs2w);
-      Sto<S>::st(fout, pix<L::Q>(j, ch), w, L::S.w[j]);
-      if (DDF) gout[pix<L::Q>(j, ch)] = vg;
+      Sto<S>::st(fout, pix<L::Q>(to), w, L::S.w[j]);
     }
+    if (DDF) gout[pix<L::Q>(to)] = vg;
   }
   if (LAM)
     for (int k = (int)blockIdx.y; k < NLAM; k += (int)gridDim.y)
@@ -1544,36 +1569,35 @@ __device__ inline T6 pick6(const T6 (&v)[6], int k) {
   return r;
 }
 
-// store of a cell's post-collision value v of population i in place at an
-// even phase (MODE 2 of the fills): to row i of the cell that pulls it
-// (through the cell's exception row), back into the cell's row opp(i) with
-// the moving-wall term at a wall, into its own row i when it pulls that
-// population from itself.  RAW copies storage values unchanged where no
-// arithmetic applies.  G: the second distribution (stored without the
+// store of a cell's post-collision value v of population i in place, in the
+// fills.  MODE 1 (odd phase): row opp(i) of the cell.  MODE 2 (even phase): row
+// i of the cell that pulls it (through the cell's exception row), back into the
+// cell's row opp(i) with the moving-wall term at a wall.  In both into its own
+// row i when it keeps that population.  RAW copies storage values unchanged
+// where no arithmetic applies.  G: the second distribution (stored without the
 // weight shift, bounced back without the moving-wall term).
-template <class L, class S, bool G = false>
+template <int MODE, class L, class S, bool G = false>
 __device__ inline void push_value(S *f, int64_t c, const int32_t *xnbr, int64_t xstride, int64_t row,
-                                  int i, typename Sto<S>::C v, S raw, bool use_raw, const double (&uw)[6][3],
+                                  uint64_t kept, int i, typename Sto<S>::C v, S raw, bool use_raw, const double (&uw)[6][3],
                                   double cs2w) {
   using C = typename Sto<S>::C;
   const int j = L::S.opp[i];
   const double wi = G ? 0.0 : L::S.w[i];
-  if (xnbr[(int64_t)(i - 1) * xstride + row] == (int32_t)c) {
-    if (use_raw) f[pix<L::Q>(i, c)] = raw;
-    else Sto<S>::st(f, pix<L::Q>(i, c), v, wi);
-  }
-  const int32_t s = xnbr[(int64_t)(j - 1) * xstride + row];
-  if (s == (int32_t)c) return;
-  if (s >= 0) {
-    if (use_raw) f[pix<L::Q>(i, s)] = raw;
-    else Sto<S>::st(f, pix<L::Q>(i, s), v, wi);
-  } else if (G) {
-    if (use_raw) f[pix<L::Q>(j, c)] = raw;
-    else Sto<S>::st(f, pix<L::Q>(j, c), v, 0.0);
+  auto put = [&](int64_t at) {
+    if (use_raw) f[at] = raw;
+    else Sto<S>::st(f, at, v, wi);
+  };
+  if ((kept >> i) & 1ull) put(pix<L::Q>(i, c));
+  const int32_t s = MODE == 1 ? -1 : xnbr[(int64_t)(j - 1) * xstride + row];
+  const int32_t cs = (int32_t)c;
+  const Word to = MODE == 1 ? even_store(j, (kept >> j) & 1ull ? cs : -1, cs) : odd_store(i, j, s, cs);
+  if (to.row < 0) return;
+  if (MODE == 1 || s >= 0 || G) {
+    put(pix<L::Q>(to));
   } else {
     C w = use_raw ? Sto<S>::ldv(raw, L::S.w[i]) : v;
     if (s <= -2) w += (C)(2.0 * L::S.w[j] * wall_dot<L>(uw, -2 - s, j) / cs2w);
-    Sto<S>::st(f, pix<L::Q>(j, c), w, L::S.w[j]);
+    Sto<S>::st(f, pix<L::Q>(to), w, L::S.w[j]);
   }
 }
 
@@ -1594,7 +1618,8 @@ __global__ void __launch_bounds__(BLOCK) k_bcfill(const BArgs a) {
   // where population i of the source and of the cell live
   const int64_t sbase = MODE == 2 ? (int64_t)a.stage[src] : src;
   auto srow = [&](int i) -> int64_t { return MODE == 1 ? L::S.opp[i] : i; };
-  const int64_t row = MODE == 2 ? (int64_t)a.bc_row[k] : 0;
+  const int64_t row = MODE != 0 ? (int64_t)a.bc_row[k] : 0;
+  const uint64_t kept = MODE != 0 ? a.xkeep[row] : 0ull;
   int kind = 0;
 #pragma unroll
   for (int q = 0; q < 6; ++q)
@@ -1619,12 +1644,12 @@ __global__ void __launch_bounds__(BLOCK) k_bcfill(const BArgs a) {
       const int i = i0 + k;
       if (i >= L::Q) break;
       const S v = vs[k], vg = DDF ? vgs[k] : S();
-      if (MODE == 2 && i > 0) {
-        push_value<L, S>(f, c, a.xnbr, a.xstride, row, i, (C)0, v, true, a.ph.uw, a.ph.cs2w);
-        if (DDF) push_value<L, S, true>(g, c, a.xnbr, a.xstride, row, i, (C)0, vg, true, a.ph.uw, 1.0);
+      if (MODE != 0 && i > 0) {
+        push_value<MODE, L, S>(f, c, a.xnbr, a.xstride, row, kept, i, (C)0, v, true, a.ph.uw, a.ph.cs2w);
+        if (DDF) push_value<MODE, L, S, true>(g, c, a.xnbr, a.xstride, row, kept, i, (C)0, vg, true, a.ph.uw, 1.0);
       } else {
-        f[pix<L::Q>(srow(i), c)] = v;
-        if (DDF) g[pix<L::Q>(srow(i), c)] = vg;
+        f[pix<L::Q>(i, c)] = v;
+        if (DDF) g[pix<L::Q>(i, c)] = vg;
       }
     }
     if (LAM)
@@ -1651,19 +1676,19 @@ __global__ void __launch_bounds__(BLOCK) k_bcfill(const BArgs a) {
 #pragma unroll
     for (int q = 0; q < NLAM; ++q) ((LamT<S> *)a.lam)[(int64_t)q * a.stride + c] = (LamT<S>)lam[q];
   }
-  if constexpr (MODE == 2) {
+  if constexpr (MODE != 0) {
     Sto<S>::st(f, pix<L::Q>(0, c), feq[0], L::S.w[0]);
     if (DDF) Sto<S>::st(g, pix<L::Q>(0, c), geq[0], 0.0);
 #pragma unroll
     for (int i = 1; i < L::Q; ++i) {
-      push_value<L, S>(f, c, a.xnbr, a.xstride, row, i, feq[i], S(), false, a.ph.uw, a.ph.cs2w);
-      if (DDF) push_value<L, S, true>(g, c, a.xnbr, a.xstride, row, i, geq[i], S(), false, a.ph.uw, 1.0);
+      push_value<MODE, L, S>(f, c, a.xnbr, a.xstride, row, kept, i, feq[i], S(), false, a.ph.uw, a.ph.cs2w);
+      if (DDF) push_value<MODE, L, S, true>(g, c, a.xnbr, a.xstride, row, kept, i, geq[i], S(), false, a.ph.uw, 1.0);
     }
   } else {
 #pragma unroll
     for (int i = 0; i < L::Q; ++i) {
-      Sto<S>::st(f, pix<L::Q>(srow(i), c), feq[i], L::S.w[i]);
-      if (DDF) Sto<S>::st(g, pix<L::Q>(srow(i), c), geq[i], 0.0);
+      Sto<S>::st(f, pix<L::Q>(i, c), feq[i], L::S.w[i]);
+      if (DDF) Sto<S>::st(g, pix<L::Q>(i, c), geq[i], 0.0);
     }
   }
 }

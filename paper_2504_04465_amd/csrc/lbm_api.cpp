@@ -13,6 +13,7 @@
 #include "grid_builder.h"
 #include "grid_device.h"
 #include "lattice.h"
+#include "inplace.h"
 #include "layout.h"
 #include "lbm.h"
 #include "mlp_ops.h"
@@ -72,6 +73,7 @@ struct lbm_ctx {
   int32_t *d_nbrick = nullptr, *d_xbase = nullptr, *d_xnbr = nullptr;
   double *d_xdu = nullptr;  // xi_i . inflow noise per explicit row [Q-1][xstride], or null
   uint64_t *d_xmask = nullptr, *d_xreg = nullptr;
+  uint64_t *d_xkeep = nullptr;  // in place: populations the rows' cells keep
   int32_t *d_cell_of = nullptr, *d_slot_of = nullptr, *d_crow = nullptr;
   uint8_t *d_flags = nullptr;
   double *d_sigma = nullptr, *d_rhoinf = nullptr;
@@ -159,7 +161,7 @@ void free_device(lbm_ctx *c) {
   c->f[0] = c->f[1] = c->gb[0] = c->gb[1] = nullptr;
   c->d_nbrick = c->d_xbase = c->d_xnbr = nullptr;
   c->d_xdu = nullptr;
-  c->d_xmask = c->d_xreg = nullptr;
+  c->d_xmask = c->d_xreg = c->d_xkeep = nullptr;
   c->d_cell_of = c->d_slot_of = c->d_crow = nullptr;
   c->d_flags = nullptr;
   c->d_gslot = nullptr;
@@ -260,6 +262,7 @@ Topo topo(const lbm_ctx *c) {
   t.xbase = c->d_xbase;
   t.xnbr = c->d_xnbr;
   t.xreg = c->d_xreg;
+  t.xkeep = c->d_xkeep;
   t.xstride = c->lay.xstride;
   t.xdu = c->d_xdu;
   t.split = c->NS <= SPLIT_SLOTS;
@@ -318,6 +321,7 @@ void launch_explode(lbm_ctx *c, int l) {
   a.xnbr = c->d_xnbr;
   a.xstride = c->lay.xstride;
   a.crow = c->d_crow;
+  a.xkeep = c->d_xkeep;
   const PhysArgs ph = phys(c, l + 1);
   a.cs2w = ph.cs2w;
   memcpy(a.uw, ph.uw, sizeof a.uw);
@@ -357,6 +361,7 @@ void launch_bcfill(lbm_ctx *c, int l) {
     a.mode = c->parity[l] == 1 ? 1 : 2;
     a.stage = c->d_gslot;
     a.bc_row = c->d_bc_row;
+    a.xkeep = c->d_xkeep;
     a.xnbr = c->d_xnbr;
     a.xstride = c->lay.xstride;
   }
@@ -921,6 +926,15 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
     // where coarse ghosts and boundary-layer sources leave their
     // post-collision populations when streaming in place
     if ((s = upload(c, &c->d_gslot, c->stage.data(), c->stage.size())) != LBM_OK) return s;
+    // the populations that fine ghosts and boundary-layer cells keep
+    std::vector<uint64_t> keep(std::max<int64_t>(y.nx, 1), 0ull);
+    for (int64_t k = 0; k < N; ++k) {
+      const int64_t r = y.xrow_of[k];
+      if (r < 0) continue;
+      for (int i = 1; i < Q; ++i)
+        if (keeps(y.xnbr[(size_t)(i - 1) * y.xstride + r], y.slot_of[k])) keep[r] |= 1ull << i;
+    }
+    if ((s = upload(c, &c->d_xkeep, keep.data(), keep.size())) != LBM_OK) return s;
     // exception row of each boundary-layer cell (its pushes go through it)
     std::vector<int32_t> br(c->g.bc_cell.size());
     for (size_t k = 0; k < br.size(); ++k) {

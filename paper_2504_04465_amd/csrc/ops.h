@@ -62,6 +62,7 @@ struct Topo {
   const int32_t *xbase;    // [bricks] first exception row of the brick
   const int32_t *xnbr;     // [Q-1][xstride] pull sources of the exception rows
   const uint64_t *xreg;    // [rows] bit i: the row's source of population i is the bulk gather's
+  const uint64_t *xkeep;   // [rows] in place: bit i: the row's cell keeps population i (its own slot is the source)
   int64_t xstride;
   const double *xdu;       // [Q-1][xstride] xi_i . (inflow noise) of the rows, or null
   int split;               // exception lanes read all sources from their rows (small 2-D grids)
@@ -158,14 +159,16 @@ struct EArgs {
   const int32_t *child, *ghost_cell;
   int64_t g0, count;
   // the coarse ghost's post-collision populations are read from its
-  // coalesced slot (vbase + ghost index, where its collide left them); mode 1, the fine level is at
-  // an odd phase: child row opp(i) takes population i; mode 2, even phase:
-  // population i goes to row i of the cell that pulls it from the child
-  // (through the child's exception row), the bounce-back into the child's
-  // own row opp(i) with the moving-wall term
+  // coalesced slot (vbase + ghost index, where its collide left them) and
+  // stored as the child's own update would have left them (inplace.h): mode 1,
+  // the fine level is at an odd phase: child row opp(i) takes population i;
+  // mode 2, even phase: population i goes to row i of the cell that pulls it
+  // from the child (through the child's exception row), the bounce-back into
+  // the child's own row opp(i) with the moving-wall term
   int mode;
   int64_t vbase, xstride;
   const int32_t *xnbr, *crow;
+  const uint64_t *xkeep;   // as in Topo
   double cs2w, uw[6][3];
 };
 
@@ -185,12 +188,12 @@ struct BArgs {
   // post-collision populations are in its own rows opp(i) (mode 1, odd
   // phase) or in its staging slot stage[src] (mode 2, even phase); the
   // boundary cell's populations are written as its own store would leave
-  // them: rows opp(i) (mode 1), or pushed through its exception row
-  // bc_row[k] (mode 2)
+  // them (inplace.h), with the sources of its exception row bc_row[k]
   int mode;
   int skip_neumann;    // the collide has filled those
   const int32_t *stage, *bc_row;
   const int32_t *xnbr;
+  const uint64_t *xkeep;   // as in Topo
   int64_t xstride;
 };
 
