@@ -31,7 +31,8 @@
 namespace lbm {
 
 // ---------------------------------------------------------------------------
-// exponential: exp(-s) = 2^n 2^(j/64) exp(r), 64 n + j = rint(-64 s / ln 2),
+// exponential, table-driven (Tang 1989, ACM TOMS 15, 144):
+// exp(-s) = 2^n 2^(j/64) exp(r), 64 n + j = rint(-64 s / ln 2),
 // |r| <= ln 2 / 128.  The Taylor polynomial of degree five leaves
 // r^6 / 720 < 4e-17 relative; the argument reduction uses ln 2 / 64 in two
 // parts.  The table holds each power and the relative remainder of its
@@ -39,8 +40,16 @@ namespace lbm {
 // remainder the multipliers' error against 80 bits grew: rms 2.8e-11 with the
 // library's exponential, 5.5e-11 without, 2.7e-11 with, 90,000 states; it
 // costs the D2Q21 collide 0.8 %).  15 vector instructions and one table read
-// where the library's exponential takes about twice as many.  n is clamped to the exponent range
-// (the results there are of the order of 1e-308 and 1e308).
+// where the library's exponential takes about twice as many.
+// The integer saturates at +-2^31 and the last operation scales by 2^n, so that
+// arguments out of range give 0 and infinity, and the subnormal ones between
+// are rounded (n clamped to the exponent range gave 1e-308 and 1e308, and n
+// from the bits of the shifted sum, 32 of them, wrapped round beyond 1.5e9: a
+// trial step of a diverging solve could find finite exponentials there and be
+// taken; both forms take the same time).  Beyond 1e13 r is no longer small; its
+// polynomial's magnitude (it may turn negative) still scales to 0 and infinity
+// up to 1e77, and above that a positive s gives infinity or NaN instead of 0: a
+// trial point with such an exponent is rejected.
 // ---------------------------------------------------------------------------
 constexpr int EXP_N = 64, EXP_TAB = 2 * EXP_N;
 
@@ -91,7 +100,8 @@ __device__ inline double exp_neg(double s, const double *tab) {
   constexpr double magic = 6755399441055744.0;  // 1.5 2^52: the sum's low bits are the rounded integer
   const double t = __builtin_fma(s, -0x1.71547652b82fep+6, magic);
   const double kf = t - magic;
-  const uint64_t k = __builtin_bit_cast(uint64_t, t);
+  int32_t k;
+  asm("v_cvt_i32_f64 %0, %1" : "=v"(k) : "v"(kf));  // (saturates; a NaN gives 0)
   double r = __builtin_fma(kf, -0x1.62e42fc000000p-7, -s);
   r = __builtin_fma(kf, -0x1.7d1cf79abc9e4p-34, r);
   double q = __builtin_fma(r, 1.0 / 120.0, 1.0 / 24.0);
@@ -99,15 +109,8 @@ __device__ inline double exp_neg(double s, const double *tab) {
   q = __builtin_fma(r, q, 0.5);
   q = __builtin_fma(r, q, 1.0);
   const uint32_t j = 2 * ((uint32_t)k & (EXP_N - 1));
-  const uint64_t tb = __builtin_bit_cast(uint64_t, tab[j]);
-  // the integer's bits 6 to 37: right up to |s| = 1.4e9, where trial steps of a
-  // diverging solve may be (a saturating conversion in place of the bits takes
-  // the network-only surrogate over its registers: 1343 -> 1607 us a pass)
-  int n = (int)(uint32_t)(k >> 6);
-  n = n < -1022 ? -1022 : (n > 1023 ? 1023 : n);
-  const uint32_t hi = (uint32_t)(tb >> 32) + ((uint32_t)n << 20);
-  const double sc = __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)tb);
-  return __builtin_fma(sc, LO ? __builtin_fma(r, q, tab[j + 1]) : r * q, sc);
+  const double p = __builtin_fma(tab[j], LO ? __builtin_fma(r, q, tab[j + 1]) : r * q, tab[j]);
+  return __builtin_amdgcn_ldexp(__builtin_fabs(p), k >> 6);
 }
 
 // ---------------------------------------------------------------------------
