@@ -194,12 +194,15 @@ __device__ inline uint64_t morton(int D, int bits, uint32_t x, uint32_t y, uint3
 // The existing cells of a level in Z order without a sort of the cells: an
 // aligned tile of 32 x 32 (8 x 8 x 8) coordinates is consecutive in Z order,
 // so only the tiles are sorted, and a cell's place is its tile's first plus
-// the existing cells before it in the tile.  One block per tile, one thread
-// per coordinate, taken in Z order.  The kernels read the state byte twice and
+// the existing cells before it in the tile.  A block takes a tile at a time, one
+// thread per coordinate, in Z order; at most TILE_BLOCKS blocks stride over the
+// tiles (several fillings of the chip: a launch may not reach 2^32 threads,
+// which the box of a sparse level can).  The kernels read the state byte twice and
 // write 13 bytes a cell; a sort of every cell's 64-bit key passed over 12
 // bytes many times.  The remesh of a three-level vortex on 1024 x 1024
 // coarse cells: sorts and scans 486 -> 150 us, the whole 3.90 -> 3.53 ms.
 constexpr int tile_bits(int D) { return D == 3 ? 3 : 5; }
+constexpr int64_t TILE_BLOCKS = 4096;
 
 struct DTiles {
   int32_t t0[3], nt[3];  // first tile and tiles per axis of the level's box
@@ -229,15 +232,17 @@ __device__ inline bool tile_cell(const DLevel &v, const DTiles &t, int32_t tile,
 template <int D>
 __global__ void __launch_bounds__(1 << (D * tile_bits(D)))
     k_tile_count(DLevel v, DTiles t, int bits, int32_t *cnt, uint64_t *keys, int32_t *ids) {
-  const int32_t tile = (int32_t)blockIdx.x;
-  int32_t q[3];
-  int64_t id;
-  const int m = __syncthreads_count(tile_cell<D>(v, t, tile, q, &id));
-  if (threadIdx.x == 0) {
-    constexpr int TB = tile_bits(D);
-    cnt[tile] = m;
-    keys[tile] = morton(D, bits, (uint32_t)(q[0] >> TB), (uint32_t)(q[1] >> TB), (uint32_t)(q[2] >> TB));
-    ids[tile] = tile;
+  const int64_t nt = t.size();
+  for (int64_t tile = blockIdx.x; tile < nt; tile += gridDim.x) {
+    int32_t q[3];
+    int64_t id;
+    const int m = __syncthreads_count(tile_cell<D>(v, t, (int32_t)tile, q, &id));
+    if (threadIdx.x == 0) {
+      constexpr int TB = tile_bits(D);
+      cnt[tile] = m;
+      keys[tile] = morton(D, bits, (uint32_t)(q[0] >> TB), (uint32_t)(q[1] >> TB), (uint32_t)(q[2] >> TB));
+      ids[tile] = (int32_t)tile;
+    }
   }
 }
 
@@ -248,21 +253,26 @@ __global__ void __launch_bounds__(1 << (D * tile_bits(D)))
                  int8_t *lev) {
   constexpr int W = (1 << (D * tile_bits(D))) / 64;
   __shared__ int32_t before[W];
-  int32_t q[3];
-  int64_t id = 0;
-  const bool ex = tile_cell<D>(v, t, ids[blockIdx.x], q, &id);
-  const unsigned long long m = __ballot(ex);
   const int wv = threadIdx.x >> 6, ln = threadIdx.x & 63;
-  if (ln == 0) before[wv] = __popcll(m);
-  __syncthreads();
-  if (!ex) return;
-  int64_t c = base + pos[blockIdx.x] + __popcll(m & ((1ull << ln) - 1));
-  for (int w = 0; w < wv; ++w) c += before[w];
-  xyz[3 * c] = q[0];
-  xyz[3 * c + 1] = q[1];
-  xyz[3 * c + 2] = q[2];
-  lev[c] = (int8_t)l;
-  v.idx[id] = (int32_t)c;
+  const int64_t nt = t.size();
+  for (int64_t k = blockIdx.x; k < nt; k += gridDim.x) {
+    int32_t q[3];
+    int64_t id = 0;
+    const bool ex = tile_cell<D>(v, t, ids[k], q, &id);
+    const unsigned long long m = __ballot(ex);
+    if (ln == 0) before[wv] = __popcll(m);
+    __syncthreads();
+    if (ex) {
+      int64_t c = base + pos[k] + __popcll(m & ((1ull << ln) - 1));
+      for (int w = 0; w < wv; ++w) c += before[w];
+      xyz[3 * c] = q[0];
+      xyz[3 * c + 1] = q[1];
+      xyz[3 * c + 2] = q[2];
+      lev[c] = (int8_t)l;
+      v.idx[id] = (int32_t)c;
+    }
+    __syncthreads();  // the next tile's counts reuse the table
+  }
 }
 
 // ---- flags, neighbour list, boundary layers, sponge --------------------------
@@ -1088,7 +1098,7 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
       t.nt[a] = a < D ? ((v.lo[a] + v.n[a] - 1) >> TB) - t.t0[a] + 1 : 1;
     }
     const int64_t nt = t.size();
-    if (nt >= INT32_MAX) return fail(err, -1, "grid too large for 32-bit cell indices");
+    if (nt >= INT32_MAX) return fail(err, -1, "level box too large for 32-bit tile indices");
     int32_t emax = std::max(v.E[0], std::max(v.E[1], D == 3 ? v.E[2] : 1));
     int bits = 0;
     while (((emax - 1) >> TB) >> bits) ++bits;
@@ -1102,7 +1112,7 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
     DEV_MEM(c0);
     DEV_MEM(c1);
     DEV_MEM(pos);
-    const dim3 tg((unsigned)nt), tt(1u << (D * TB));
+    const dim3 tg((unsigned)std::min(nt, TILE_BLOCKS)), tt(1u << (D * TB));
     if (D == 3) hipLaunchKernelGGL(k_tile_count<3>, tg, tt, 0, st, v, t, bits, c0, k0, i0);
     else hipLaunchKernelGGL(k_tile_count<2>, tg, tt, 0, st, v, t, bits, c0, k0, i0);
     size_t tb = 0;
@@ -1153,7 +1163,7 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
   DEV_MEM(pos);
   for (int l = 0; l < L; ++l)
     if (cnt[l] > 0) {
-      const dim3 tg((unsigned)tiles[l].size()), tt(1u << (D * tile_bits(D)));
+      const dim3 tg((unsigned)std::min(tiles[l].size(), TILE_BLOCKS)), tt(1u << (D * tile_bits(D)));
       if (D == 3)
         hipLaunchKernelGGL(k_tile_place<3>, tg, tt, 0, st, G.lv[l], tiles[l], ord[l], first[l], g.off[l], l, xyz, lev);
       else

@@ -164,3 +164,24 @@ def test_device_order_at_tile_edges(ext):
     same_grid(*sims, ext)
     for s in sims:
         s.close()
+
+
+@pytest.mark.parametrize("ext,keep", [((2200, 2100), 0.7), ((130, 136, 140), 0.7), ((4100, 2100), 1e-3)],
+                         ids=lambda e: str(e))
+def test_device_order_of_many_tiles(ext, keep):
+    """levels whose box has more tiles (4,554, 5,202 and 8,514) than the
+    4,096 blocks that order them, dense and sparse"""
+    D = len(ext)
+    rng = np.random.default_rng(sum(ext))
+    solid = [W.Mask((rng.random(ext[::-1]) > keep).astype(np.uint8), (0,) * D)]
+    faces = [W.Face("wall") for _ in range(2 * D)]
+    got = []
+    for device in (True, False):
+        s = B.LBM("D2Q9" if D == 2 else "D3Q27", "RR", "fp32", nu_finest=0.01, T0=1.0 / 3.0)
+        s.device_build(device)
+        s.grid(D, ext, 1, [], solid, faces)
+        got.append((s.export(("coords", "level", "flags")), s.layout_export()))
+        s.close()
+    for a, b in zip(*got):
+        for k in a:
+            assert np.array_equal(a[k], b[k]), k
