@@ -197,14 +197,15 @@ lbm_status lbm_layout_info(lbm_ctx *ctx, int64_t *n_slots, int64_t *n_exception_
  * rows; xnbr [Q-1][n_rows] the pull sources of the exception rows (slot,
  * coalesced slot >= n_slots, -1 bounce-back, -2 - k moving wall of face k).
  * Sizes from lbm_layout_info; any pointer may be NULL.  Errors: LBM_E_ARG,
- * LBM_E_STATE (no grid). */
+ * LBM_E_STATE (no grid), LBM_E_DEVICE (a device-built grid's tables could not
+ * be copied; a later call tries again). */
 lbm_status lbm_layout_export(lbm_ctx *ctx, int32_t *slot_of, int32_t *xrow_of, int32_t *nbrick, uint64_t *xmask,
                              int32_t *xnbr);
 
 /* Export the tables in canonical form (any pointer may be NULL):
  * coords [n][3], level [n], flags [n], nbr [n][Q-1] (sentinels above),
  * child [n_coarse_ghosts][2^D] (octant o = cx | cy<<1 | cz<<2, -1 missing),
- * bc_src [n] (-1 for non-boundary cells). */
+ * bc_src [n] (-1 for non-boundary cells).  Errors: as lbm_layout_export. */
 lbm_status lbm_grid_export(lbm_ctx *ctx, int32_t *coords, int8_t *level,
                            uint8_t *flags, int32_t *nbr, int32_t *child,
                            int32_t *bc_src);

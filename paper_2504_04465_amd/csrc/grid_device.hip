@@ -13,6 +13,8 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <new>
+#include <utility>
 #include <vector>
 
 // the sponge ramp is evaluated in the host builder's operation order
@@ -1491,42 +1493,82 @@ int build_grid_device(const LatticeInfo &lat, int dim, const int32_t ext_in[3], 
   return 0;
 }
 
-int fetch_host_grid(const DeviceGridArrays &dg, HostGrid *g, hipStream_t st, std::string *err) {
+// Both fetches fill tables of their own and hand them over whole: after a
+// failure half way (a stream that is being captured, no host memory) the
+// caller's are as empty as before, and the next call tries again.
+namespace {
+// waits for copies still under way before their host arrays go
+struct Drain {
+  hipStream_t st;
+  ~Drain() { (void)hipStreamSynchronize(st); }
+};
+}  // namespace
+
+int fetch_host_grid(const DeviceGridArrays &dg, HostGrid *g, hipStream_t st, std::string *err) try {
   if (!dg.xyz || !g->xyz.empty() || dg.n == 0) return 0;
-  DEV_TRY(down(g->xyz, dg.xyz, 3 * dg.n, st));
-  DEV_TRY(down(g->lev, dg.lev, dg.n, st));
-  DEV_TRY(down(g->flag, dg.flag, dg.n, st));
-  DEV_TRY(down(g->ghost_cell, dg.ghost, dg.ng, st));
-  DEV_TRY(down(g->child, dg.child, (size_t)dg.ng * dg.nch, st));
-  DEV_TRY(down(g->unknown, dg.unknown, dg.ng, st));
-  DEV_TRY(down(g->bc_cell, dg.bc_cell, dg.nbc, st));
-  DEV_TRY(down(g->bc_src, dg.bc_src, dg.nbc, st));
-  DEV_TRY(down(g->bc_face, dg.bc_face, dg.nbc, st));
-  DEV_TRY(hipStreamSynchronize(st));
-  g->bc_src_all.assign((size_t)dg.n, -1);
-  for (size_t k = 0; k < g->bc_cell.size(); ++k) g->bc_src_all[g->bc_cell[k]] = g->bc_src[k];
+  HostGrid h;
+  {
+    Drain wait{st};
+    DEV_TRY(down(h.xyz, dg.xyz, 3 * dg.n, st));
+    DEV_TRY(down(h.lev, dg.lev, dg.n, st));
+    DEV_TRY(down(h.flag, dg.flag, dg.n, st));
+    DEV_TRY(down(h.ghost_cell, dg.ghost, dg.ng, st));
+    DEV_TRY(down(h.child, dg.child, (size_t)dg.ng * dg.nch, st));
+    DEV_TRY(down(h.unknown, dg.unknown, dg.ng, st));
+    DEV_TRY(down(h.bc_cell, dg.bc_cell, dg.nbc, st));
+    DEV_TRY(down(h.bc_src, dg.bc_src, dg.nbc, st));
+    DEV_TRY(down(h.bc_face, dg.bc_face, dg.nbc, st));
+    DEV_TRY(hipStreamSynchronize(st));
+  }
+  h.bc_src_all.assign((size_t)dg.n, -1);
+  for (size_t k = 0; k < h.bc_cell.size(); ++k) h.bc_src_all[h.bc_cell[k]] = h.bc_src[k];
+  g->xyz = std::move(h.xyz);
+  g->lev = std::move(h.lev);
+  g->flag = std::move(h.flag);
+  g->ghost_cell = std::move(h.ghost_cell);
+  g->child = std::move(h.child);
+  g->unknown = std::move(h.unknown);
+  g->bc_cell = std::move(h.bc_cell);
+  g->bc_src = std::move(h.bc_src);
+  g->bc_face = std::move(h.bc_face);
+  g->bc_src_all = std::move(h.bc_src_all);
   return 0;
+} catch (const std::bad_alloc &) {
+  return fail(err, -3, "host copy of the grid: allocation failed");
 }
 
-int fetch_host_layout(const DeviceGridArrays &dg, DeviceLayout *y, hipStream_t st, std::string *err) {
+int fetch_host_layout(const DeviceGridArrays &dg, DeviceLayout *y, hipStream_t st, std::string *err) try {
   if (!dg.xyz || !y->slot_of.empty() || dg.n == 0) return 0;
   const int64_t nbrk = dg.nslot / 64;
+  DeviceLayout h;
   std::vector<unsigned long long> xm;
-  DEV_TRY(down(y->slot_of, dg.slot_of, dg.n, st));
-  DEV_TRY(down(y->cell_of, dg.cell_of, dg.nslot, st));
-  DEV_TRY(down(y->nbrick, dg.nbrick, (size_t)nbrk * dg.nbp, st));
-  DEV_TRY(down(xm, dg.xmask, nbrk, st));
-  DEV_TRY(down(y->xbase, dg.xbase, nbrk, st));
-  DEV_TRY(down(y->xnbr, dg.xnbr, (size_t)dg.Qm * dg.xstride, st));
-  DEV_TRY(hipStreamSynchronize(st));
-  y->xmask.assign(xm.begin(), xm.end());
-  y->xrow_of.assign((size_t)dg.n, -1);
-  for (int64_t c = 0; c < dg.n; ++c) {
-    const int64_t s = y->slot_of[c], b = s / 64;
-    if ((y->xmask[b] >> (s & 63)) & 1ull)
-      y->xrow_of[c] = y->xbase[b] + __builtin_popcountll(y->xmask[b] & ((1ull << (s & 63)) - 1ull));
+  {
+    Drain wait{st};
+    DEV_TRY(down(h.slot_of, dg.slot_of, dg.n, st));
+    DEV_TRY(down(h.cell_of, dg.cell_of, dg.nslot, st));
+    DEV_TRY(down(h.nbrick, dg.nbrick, (size_t)nbrk * dg.nbp, st));
+    DEV_TRY(down(xm, dg.xmask, nbrk, st));
+    DEV_TRY(down(h.xbase, dg.xbase, nbrk, st));
+    DEV_TRY(down(h.xnbr, dg.xnbr, (size_t)dg.Qm * dg.xstride, st));
+    DEV_TRY(hipStreamSynchronize(st));
   }
+  h.xmask.assign(xm.begin(), xm.end());
+  h.xrow_of.assign((size_t)dg.n, -1);
+  for (int64_t c = 0; c < dg.n; ++c) {
+    const int64_t s = h.slot_of[c], b = s / 64;
+    if ((h.xmask[b] >> (s & 63)) & 1ull)
+      h.xrow_of[c] = h.xbase[b] + __builtin_popcountll(h.xmask[b] & ((1ull << (s & 63)) - 1ull));
+  }
+  y->slot_of = std::move(h.slot_of);
+  y->cell_of = std::move(h.cell_of);
+  y->nbrick = std::move(h.nbrick);
+  y->xmask = std::move(h.xmask);
+  y->xbase = std::move(h.xbase);
+  y->xnbr = std::move(h.xnbr);
+  y->xrow_of = std::move(h.xrow_of);
   return 0;
+} catch (const std::bad_alloc &) {
+  return fail(err, -3, "host copy of the layout: allocation failed");
 }
 
 namespace {

@@ -5,6 +5,8 @@ integer, on the small parity grids, the ragged and degenerate edge cases,
 and full-size workloads; invalid masks must fail with the same code and
 text; a run and a remesh on the device-built grid must give the same bits
 as on the host-built one."""
+import ctypes
+import resource
 import time
 
 import numpy as np
@@ -185,3 +187,28 @@ def test_device_order_of_many_tiles(ext, keep):
     for a, b in zip(*got):
         for k in a:
             assert np.array_equal(a[k], b[k]), k
+
+
+def test_export_without_host_memory():
+    """an export that cannot have the host memory for its copy says so, and the
+    next one gives the tables whole"""
+    w = W.shear(n=1600, levels=2, steps=1)  # 12 MB and more a table: each a mapping of its own
+    ref, _ = build(w, False)
+    s, _ = build(w, True)
+    n, nb = s.n, s.layout()["slots"] // 64
+    coords, xmask = np.zeros((n, 3), np.int32), np.zeros(nb, np.uint64)
+    none, ptr = ctypes.c_void_p(), lambda a: a.ctypes.data_as(ctypes.c_void_p)
+    calls = [lambda: s._L.lbm_grid_export(s.h, ptr(coords), none, none, none, none, none),
+             lambda: s._L.lbm_layout_export(s.h, none, none, none, ptr(xmask), none)]
+    pages = int(open("/proc/self/statm").read().split()[0])
+    old = resource.getrlimit(resource.RLIMIT_AS)
+    resource.setrlimit(resource.RLIMIT_AS, (pages * resource.getpagesize() + (4 << 20), old[1]))
+    try:
+        codes = [c() for c in calls]
+    finally:
+        resource.setrlimit(resource.RLIMIT_AS, old)
+    assert codes == [-4, -4]  # LBM_E_DEVICE
+    assert not coords.any() and not xmask.any()
+    same_grid(s, ref, "after a failed copy")
+    s.close()
+    ref.close()
