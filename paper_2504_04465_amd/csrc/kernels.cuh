@@ -1575,14 +1575,15 @@ __device__ inline T6 pick6(const T6 (&v)[6], int k) {
 // cell's row opp(i) with the moving-wall term at a wall.  In both into its own
 // row i when it keeps that population.  RAW copies storage values unchanged
 // where no arithmetic applies.  G: the second distribution (stored without the
-// weight shift, bounced back without the moving-wall term).
-template <int MODE, class L, class S, bool G = false>
+// weight shift, bounced back without the moving-wall term).  SHIFTED: v is
+// already f_i - w_i.
+template <int MODE, class L, class S, bool G = false, bool SHIFTED = false>
 __device__ inline void push_value(S *f, int64_t c, const int32_t *xnbr, int64_t xstride, int64_t row,
                                   uint64_t kept, int i, typename Sto<S>::C v, S raw, bool use_raw, const double (&uw)[6][3],
                                   double cs2w) {
   using C = typename Sto<S>::C;
   const int j = L::S.opp[i];
-  const double wi = G ? 0.0 : L::S.w[i];
+  const double wi = G || SHIFTED ? 0.0 : L::S.w[i];
   auto put = [&](int64_t at) {
     if (use_raw) f[at] = raw;
     else Sto<S>::st(f, at, v, wi);
@@ -1597,7 +1598,7 @@ __device__ inline void push_value(S *f, int64_t c, const int32_t *xnbr, int64_t 
   } else {
     C w = use_raw ? Sto<S>::ldv(raw, L::S.w[i]) : v;
     if (s <= -2) w += (C)(2.0 * L::S.w[j] * wall_dot<L>(uw, -2 - s, j) / cs2w);
-    Sto<S>::st(f, pix<L::Q>(to), w, L::S.w[j]);
+    Sto<S>::st(f, pix<L::Q>(to), w, use_raw ? L::S.w[j] : wi);
   }
 }
 
@@ -1677,11 +1678,23 @@ __global__ void __launch_bounds__(BLOCK) k_bcfill(const BArgs a) {
     for (int q = 0; q < NLAM; ++q) ((LamT<S> *)a.lam)[(int64_t)q * a.stride + c] = (LamT<S>)lam[q];
   }
   if constexpr (MODE != 0) {
-    Sto<S>::st(f, pix<L::Q>(0, c), feq[0], L::S.w[0]);
+    // all of the equilibrium before the conditional stores, as MODE 0 has it
+    // (FP16: with the subtraction of the weight): moved into their branches its
+    // multiplications and additions would be fused differently, and rounded
+    // differently from two buffers
+    constexpr bool SHIFTED = std::is_same<S, __half>::value;
+#pragma unroll
+    for (int i = 0; i < L::Q; ++i) {
+      if (SHIFTED) feq[i] -= (C)L::S.w[i];
+      asm volatile("" : "+v"(feq[i]));
+      if (DDF) asm volatile("" : "+v"(geq[i]));
+    }
+    Sto<S>::st(f, pix<L::Q>(0, c), feq[0], SHIFTED ? 0.0 : L::S.w[0]);
     if (DDF) Sto<S>::st(g, pix<L::Q>(0, c), geq[0], 0.0);
 #pragma unroll
     for (int i = 1; i < L::Q; ++i) {
-      push_value<MODE, L, S>(f, c, a.xnbr, a.xstride, row, kept, i, feq[i], S(), false, a.ph.uw, a.ph.cs2w);
+      push_value<MODE, L, S, false, SHIFTED>(f, c, a.xnbr, a.xstride, row, kept, i, feq[i], S(), false, a.ph.uw,
+                                             a.ph.cs2w);
       if (DDF) push_value<MODE, L, S, true>(g, c, a.xnbr, a.xstride, row, kept, i, geq[i], S(), false, a.ph.uw, 1.0);
     }
   } else {

@@ -1,14 +1,26 @@
-"""Interfaces that are not boxes (re-entrant corners, staircases, balls): in
-place against two buffers, bit for bit after odd and even step counts, and
-both against the oracle at the FP64 bounds of every parity test."""
+"""Interfaces that are not boxes (re-entrant corners, staircases, balls),
+interfaces that a body cuts into, and equilibrium and Neumann faces on one
+level: in place against two buffers, bit for bit after odd and even step
+counts, levels in one launch against one launch each, and all of them against
+the oracle at the FP64 bounds of every parity test.
+
+Which kernels that runs: with two buffers the collide explodes (with children
+missing, child by child) and, in the BGK, RR and polynomial models, fills the
+Neumann cells of a level, while the boundary kernel is left its equilibrium
+cells; Newton models and in-place runs launch the kernels for all of it."""
 import numpy as np
 import pytest
 
 from gpu_util import assert_within, compare, run_pair, say
-from interface_cases import patch_cases
+from interface_cases import cut_cases, open_cases, patch_cases
 from paper_2504_04465_amd import lbm as B
+from paper_2504_04465_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
+
+
+CASES = patch_cases() + cut_cases() + open_cases()
+IDS = [c[0] for c in CASES]
 
 
 def same_state(a, b, what):
@@ -22,30 +34,50 @@ def same_state(a, b, what):
 
 
 @pytest.mark.parametrize("storage", ["fp64", "fp32", "fp16"])
-@pytest.mark.parametrize("name,w", patch_cases(), ids=[c[0] for c in patch_cases()])
-def test_in_place_equals_two_buffers_on_patches(name, w, storage):
+@pytest.mark.parametrize("name,w", CASES, ids=IDS)
+def test_in_place_equals_two_buffers(name, w, storage):
     if storage == "fp16" and w.collision.startswith("DDF"):
         pytest.skip("FP16 storage is refused with two distributions")
     a = B.LBM.from_workload(w, storage=storage)
     b = B.LBM.from_workload(w, storage=storage, in_place=True)
+    c = B.LBM.from_workload(w, storage=storage)
+    c.level_fusion(False)
     m0 = w.initial_moments(*a.coords_levels())
-    a.init(m0)
-    b.init(m0)
+    for s in (a, b, c):
+        s.init(m0)
     for n in (1, 1, 2, 5):
-        a.step(n)
-        b.step(n)
-        same_state(a, b, (name, n))
-    say(f"[in-place] {name} {storage}: identical")
-    a.close()
-    b.close()
+        for s in (a, b, c):
+            s.step(n)
+        same_state(a, b, (name, n, "in place"))
+        same_state(a, c, (name, n, "a launch per level"))
+    say(f"[shapes] {name} {storage}: identical")
+    for s in (a, b, c):
+        s.close()
 
 
 @pytest.mark.parametrize("in_place", [False, True], ids=["two buffers", "in place"])
-@pytest.mark.parametrize("name,w", patch_cases(), ids=[c[0] for c in patch_cases()])
-def test_patches_against_oracle(name, w, in_place):
+@pytest.mark.parametrize("name,w", CASES, ids=IDS)
+def test_against_oracle(name, w, in_place):
     w.newton_tol = 1e-14  # (both sides stop well below the bound compared at)
     mg, mo, level, s, o = run_pair(w, 5, "fp64", lib_over={"in_place": in_place})
     err = compare(mg, mo, level, len(w.ext))
-    say(f"[patch] {name} in_place={in_place}: {err}")
+    say(f"[shapes] {name} in_place={in_place}: {err}")
+    assert_within(err, 1e-12)
+    s.close()
+
+
+@pytest.mark.parametrize("in_place", [False, True], ids=["two buffers", "in place"])
+def test_wide_boundary_layer_of_a_newton_model(in_place):
+    """66,000 boundary cells on one level, half Neumann and half equilibrium:
+    the boundary kernel with several populations per lane"""
+    w = W.shear(n=16, levels=1, lattice="D2Q21", collision="DDF_NEWTON", kind="random", u0=0.03, nu_finest=0.05,
+                T0=0.65)
+    w.ext = (11000, 20)
+    w.newton_tol = 1e-14
+    w.faces = [W.Face(), W.Face(), W.Face("neumann"),
+               W.Face("equilibrium", u=(0.03, 0.01, 0.0), T=0.65, extrapolate_rho=True), W.Face(), W.Face()]
+    mg, mo, level, s, o = run_pair(w, 3, "fp64", lib_over={"in_place": in_place})
+    err = compare(mg, mo, level, 2)
+    say(f"[shapes] wide boundary layer in_place={in_place}: {err}")
     assert_within(err, 1e-12)
     s.close()

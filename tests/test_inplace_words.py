@@ -12,7 +12,7 @@ import numpy as np
 import pytest
 
 from edge_cases import edge_cases
-from interface_cases import patch_cases
+from interface_cases import cut_cases, open_cases, patch_cases
 from oracle.oracle import Oracle
 from paper_2504_04465_amd import lbm as B
 from paper_2504_04465_amd import workloads as W
@@ -104,7 +104,7 @@ def grids():
             ("D2Q13", W.shear(n=32, levels=3, lattice="D2Q13", collision="DDF_NEWTON", T0=0.35)),
             ("cylinder", W.cylinder(scale=16, steps=1)), ("sphere", W.sphere(scale=8, steps=1)),
             ("airfoil", W.airfoil(scale=16, steps=1)), ("Sod", W.sod(nx=256, ny=8, steps=1))]
-    return base + edge_cases() + patch_cases()
+    return base + edge_cases() + patch_cases() + cut_cases() + open_cases()
 
 
 @pytest.mark.parametrize("name,w", grids(), ids=[g[0] for g in grids()])
@@ -121,4 +121,14 @@ def test_odd_step_words_have_one_user(name, w, check):
     assert races == 0 and wrong == 0
     if s.n_ghosts:
         assert kept > 0  # fine ghosts at the edge of their level
+    s.close()
+
+
+@pytest.mark.parametrize("name,w", cut_cases(), ids=[c[0] for c in cut_cases()])
+def test_cut_cases_cut(name, w):
+    """the grids meant to have coarse ghosts with one to all but one of their
+    children missing do"""
+    s = B.LBM.from_workload(w, storage="fp32", host_only=True)
+    missing = (s.export(("child",))["child"] < 0).sum(1)
+    assert {1, 2, (1 << len(w.ext)) - 1} <= set(missing.tolist()) and (missing == 0).sum() > 0
     s.close()
