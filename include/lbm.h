@@ -107,11 +107,12 @@ typedef struct {
                               (AA pattern: even steps read and write the
                               cell's own rows, the opposite row for the
                               result; odd steps pull from and push to the
-                              neighbours), half the population memory.  One
-                              level only, periodic / wall / moving-wall
-                              faces, no sponge, no surrogate; otherwise
-                              lbm_grid_build returns LBM_E_UNSUPPORTED.
-                              Results are identical to two buffers.      */
+                              neighbours), half the population memory.  Any
+                              levels and faces; not with the surrogate
+                              (lbm_grid_build returns LBM_E_UNSUPPORTED),
+                              inflow noise or lbm_remesh.  Results are
+                              identical to two buffers, but for one more
+                              rounding at moving walls with FP16 storage. */
 } lbm_params;
 
 typedef struct {
@@ -162,10 +163,10 @@ lbm_status lbm_grid_build(lbm_ctx *ctx, int dim, const int32_t ext_coarse[3],
  * layout (Secs. 4.3-4.4; Sec. 8 names the host-side tree construction as
  * the cost of remeshing): on = 1 (the default) builds them on the GPU,
  * every rule of the construction applied per cell in parallel (Z order by
- * a radix sort of Morton keys, lists by prefix sums), and keeps the result
+ * a radix sort of tiles of cells, lists by prefix sums), and keeps the result
  * there: readers of the tables (lbm_grid_export, lbm_layout_export,
- * lbm_set_inflow_noise, in-place builds) copy them to the host the first
- * time they need them; on = 0 builds them on the host.  Both give
+ * lbm_set_inflow_noise, in-place builds) copy all of them to the host the
+ * first time they need any; on = 0 builds them on the host.  Both give
  * the same grid value for value and the same errors.  Host-only contexts
  * always build on the host.  Takes effect at the next build.  Errors:
  * LBM_E_ARG (null context). */

@@ -33,9 +33,10 @@ constexpr int BLOCK = 256;
 
 // ---------------------------------------------------------------------------
 // storage traits: FP64, FP32, FP16 holding f_i - w_i (compute in FP32).
-// stn (stg, on a global pointer; sta is its plain form) is a streaming (non-temporal) store: the collide kernel's output is not
-// read again before the level's next update, so it should not displace the
-// neighbour lines that other wavefronts still pull from the L2.
+// stn (stg, on a global pointer; sta is its plain form) is a streaming
+// (non-temporal) store: the collide kernel's output is not read again before
+// the level's next update, so it should not displace the neighbour lines that
+// other wavefronts still pull from the L2.
 // ---------------------------------------------------------------------------
 // pointers into global memory (address space 1): accesses through them are
 // global, not flat, instructions, which take an SGPR base plus a VGPR offset
@@ -354,7 +355,8 @@ __device__ inline void gather(const S *fin, const S *gin, const Topo &tp, const 
 // go through the L2 (sta), which merges the parts that meet there; streaming
 // stores (as the pull's whole lines take) made the odd step of a 160 x 80 x 80
 // sphere 59.1 us a launch instead of 55.4.  With 32-bit offsets (O32, buffers
-// under 4 GB) it is 52.2; the even step, which writes whole lines, 26.7.
+// under 4 GB) it is 54.2 (52.2 while kept populations were read in row opp(i),
+// inplace.h); the even step, which writes whole lines, 28.5 (26.7).
 template <class L, class S, bool DDF, bool RAW = false, bool O32 = false>
 __device__ inline void push_store(S *fout, S *gout, const Topo &tp, const uint32_t *nbs, int64_t c,
                                   int lane, int32_t brick, uint64_t xm, const double (&uw)[6][3], double cs2w,
@@ -432,7 +434,8 @@ __device__ inline void push_store(S *fout, S *gout, const Topo &tp, const uint32
 
 // After the rows of an even step (row opp(i) holds population i): the
 // populations that cell c keeps, each in its own row (even_store).  Only fine
-// ghosts and boundary cells have any.
+// ghosts and boundary cells have any; a mask per exception row names them (the
+// row's 26 links read again instead: sphere in place 1581 against 1516 us).
 template <class L, class S, bool DDF, bool RAW>
 __device__ inline void keep_store(S *fout, S *gout, const Topo &tp, int64_t c, const typename Sto<S>::C *f,
                                   const typename Sto<S>::C *g) {
@@ -795,8 +798,9 @@ __device__ inline void rr_hermite3(C *f, C rho, C rhop, const C *u, const C (&P)
 // kinetic sensor, Eqs. DeltaAvg and shock_function
 // ---------------------------------------------------------------------------
 // n / d for the sensor's mean of Q ratios: the hardware reciprocal and one
-// correction of the quotient (within an ulp; d is at least 1e-30), 4
-// instructions where the IEEE division takes 10
+// correction of the quotient (d is at least 1e-30), 4 instructions where the
+// IEEE division takes 10; with the reciprocal an ulp off either way, 2e7
+// sampled quotients all came out correctly rounded
 __device__ inline float ratio(float n, float d) {
   const float r = __builtin_amdgcn_rcpf(d);
   const float q = n * r;
@@ -1412,8 +1416,10 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
 // compute units idle.  Above, a lane's table reads serve several populations,
 // whose loads are in flight together: four of them (coalescence on the
 // sphere, 31 k ghosts of 8 children: 29.3 us a launch with one, 26.2 with
-// four, 28.2 with all 27).  On the cylinder's interfaces (up to 37 k lanes)
-// four instead of one cost 2.5 % of the step.
+// four, 28.2 with all 27; explosion in place, four steps of the 160 x 80 x 80
+// sphere with 1, 2, 4, 9 and 27 a lane: 1589, 1569, 1551, 1556, 1596 us).  On
+// the cylinder's interfaces (up to 37 k lanes) four instead of one cost 2.5 %
+// of the step.
 // ---------------------------------------------------------------------------
 constexpr int64_t POPS_WIDE = 65536;
 

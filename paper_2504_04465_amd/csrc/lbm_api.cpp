@@ -252,7 +252,7 @@ const void *gbuf(const lbm_ctx *c, int l) { return c->gb[c->parity[l]]; }
 // four fillings of the chip by the collide (256 compute units x 8 wavefronts):
 // up to there the split pull is the shorter one (refined D2Q9 cavity, us per
 // step without / with: 117 k slots FP32 16.7 / 15.0, 261 k 18.4 / 17.1, 463 k
-// 23.4 / 22.7; on the cylinder's 7 M slots it costs 0.8 %)
+// 23.4 / 22.7; on the cylinder's 7 M slots it costs 1.1 %)
 constexpr int64_t SPLIT_SLOTS = 4 * 256 * 8 * 64;
 
 Topo topo(const lbm_ctx *c) {
@@ -861,7 +861,7 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
       // device flags per slot: the canonical ones, F_MOVING where a population
       // is pulled from a moving wall, F_HOLE for slots without a cell
       std::vector<uint8_t> fl(NS, (uint8_t)F_HOLE);
-  #pragma omp parallel for schedule(static)
+#pragma omp parallel for schedule(static)
       for (int64_t cc = 0; cc < N; ++cc) {
         uint8_t v = c->g.flag[cc];
         for (int i = 0; i < Qm; ++i)
@@ -1778,7 +1778,7 @@ lbm_status lbm_mlp_train(lbm_ctx *c, const double *x, const double *lambda, int6
     HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
   // canonical octant, output normalisation from the labels, normalised
-  // samples: on the device, while the host shuffles the first epoch
+  // samples: on the device, the kernels while the host shuffles the first epoch
   CallBuffers tmp(c);
   double *rx = (double *)tmp.take(sizeof(double) * 4 * n);
   double *rl = (double *)tmp.take(sizeof(double) * 8 * n);
@@ -1795,7 +1795,6 @@ lbm_status lbm_mlp_train(lbm_ctx *c, const double *x, const double *lambda, int6
   c->have_mlp = true;
   HIP_TRY(c, hipMemsetAsync(c->d_mlp_m, 0, sizeof(float) * MLP_PARAMS, c->stream));
   HIP_TRY(c, hipMemsetAsync(c->d_mlp_v, 0, sizeof(float) * MLP_PARAMS, c->stream));
-  HIP_TRY(c, hipMemsetAsync(c->d_mlp_g, 0, sizeof(float) * MLP_PARAMS, c->stream));
   const int64_t nb = n / batch;
   const int64_t total = nb * epochs;
   std::vector<int32_t> perm(n);
