@@ -437,10 +437,10 @@ __device__ inline void push_store(S *fout, S *gout, const Topo &tp, const uint32
 // ghosts and boundary cells have any; a mask per exception row names them (the
 // row's 26 links read again instead: sphere in place 1581 against 1516 us).
 template <class L, class S, bool DDF, bool RAW>
-__device__ inline void keep_store(S *fout, S *gout, const Topo &tp, int64_t c, const typename Sto<S>::C *f,
-                                  const typename Sto<S>::C *g) {
+__device__ inline void keep_store(S *fout, S *gout, const Topo &tp, const uint64_t *xkeep, int64_t c,
+                                  const typename Sto<S>::C *f, const typename Sto<S>::C *g) {
   // the mask is read again rather than held across the collision
-  const uint64_t kept = tp.xkeep[tp.xbase[c >> 6] + __popcll(tp.xmask[c >> 6] & ((1ull << (c & 63)) - 1ull))];
+  const uint64_t kept = xkeep[tp.xbase[c >> 6] + __popcll(tp.xmask[c >> 6] & ((1ull << (c & 63)) - 1ull))];
 #pragma unroll
   for (int i = 1; i < L::Q; ++i)
     if ((kept >> i) & 1ull) {
@@ -1392,7 +1392,7 @@ __global__ void __launch_bounds__((CollideBlock<L, COLL>::value))
   }
   if constexpr (AA == 1) {
     if (fl & (F_FINE_GHOST | F_BC_NEUMANN | F_BC_EQ))
-      keep_store<L, S, DDF, SH>(fout, gout, a.topo, c, f, g);
+      keep_store<L, S, DDF, SH>(fout, gout, a.topo, a.xkeep, c, f, g);
   }
   if constexpr (FILL) {
     if ((fl & F_BC_SOURCE) && a.fill.off) fill_store<L, S, DDF, SH>(a.fill, fout, gout, c, f, g);

@@ -262,7 +262,6 @@ Topo topo(const lbm_ctx *c) {
   t.xbase = c->d_xbase;
   t.xnbr = c->d_xnbr;
   t.xreg = c->d_xreg;
-  t.xkeep = c->d_xkeep;
   t.xstride = c->lay.xstride;
   t.xdu = c->d_xdu;
   t.split = c->NS <= SPLIT_SLOTS;
@@ -402,6 +401,7 @@ KArgs collide_args(lbm_ctx *c, int l, int par) {
   a.counters = c->d_counters;
   a.gslot = c->d_gslot;
   a.xghost = c->d_xghost;
+  a.xkeep = c->d_xkeep;
   a.child = c->d_child;
   a.fill = c->fill;
   return a;
