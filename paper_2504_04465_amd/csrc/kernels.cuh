@@ -234,7 +234,10 @@ __device__ inline void gather_row(const S *fin, const S *gin, const int32_t *xnb
     const int32_t s = sv[i];
     int64_t idx;
     if (PRE) idx = pix<L::Q>(i, (int64_t)s >= vbase ? (int64_t)s : c);
-    else if (AA == 2) idx = pix<L::Q>(odd_pull(i, L::S.opp[i], s, (int32_t)c));
+    else if (AA == 2)
+      // (whole addresses are selected: a selected row and slot take a third
+      // more registers in the read-backs, moments 380 -> 415 us)
+      idx = odd_pull(i, L::S.opp[i], s, (int32_t)c).row != i ? pix<L::Q>(L::S.opp[i], s) : pix<L::Q>(i, c);
     else idx = s >= 0 ? pix<L::Q>(i, s) : pix<L::Q>(L::S.opp[i], c);
     // the lattice is symmetric: w of the opposite population is w_i
     f[i] = RAW ? Sto<S>::ldr(fin[idx]) : Sto<S>::ld(fin, idx, L::S.w[i]);
