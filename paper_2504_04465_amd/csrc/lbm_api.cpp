@@ -928,6 +928,7 @@ lbm_status lbm_grid_build(lbm_ctx *c, int dim, const int32_t ext[3], int n_level
     if ((s = upload(c, &c->d_gslot, c->stage.data(), c->stage.size())) != LBM_OK) return s;
     // the populations that fine ghosts and boundary-layer cells keep
     std::vector<uint64_t> keep(std::max<int64_t>(y.nx, 1), 0ull);
+#pragma omp parallel for schedule(static)
     for (int64_t k = 0; k < N; ++k) {
       const int64_t r = y.xrow_of[k];
       if (r < 0) continue;
